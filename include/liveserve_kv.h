@@ -226,19 +226,25 @@ ls_status paged_attn_decode_static(ls_kv_pool *pool, int32_t layer, int32_t num_
  *                  c_s + n_s tokens
  *   out            device bf16 [total_new_tokens][num_q_heads][head_dim]
  *   workspace      optional device memory (16-byte aligned) of workspace_bytes >=
- *                  LS_PREFILL_WORKSPACE_BYTES, or NULL (LS_ENOMEM if too small,
- *                  LS_EINVAL if misaligned).  With host lengths the workgroups then stay
- *                  resident, one per CU, and take query tiles in order through a
- *                  counter per XCD kept here; an XCD whose tiles run out takes the next
+ *                  LS_PREFILL_COUNTER_BYTES, or NULL (LS_ENOMEM if too small,
+ *                  LS_EINVAL if misaligned).  With host lengths the workgroups
+ *                  take query tiles in order through a counter per XCD kept here;
+ *                  an XCD whose tiles run out takes the next
  *                  tiles of the XCD with the most left, so XCDs of different speeds
  *                  finish together.  The call clears it first (its contents on entry do
- *                  not matter).  Calls that may run at the same time need different
+ *                  not matter).  With LS_PREFILL_WORKSPACE_BYTES or more, calls with too
+ *                  few query tiles to fill the GPU also split long tiles' keys over
+ *                  several workgroups, whose fp32 partial results are kept here and
+ *                  added up by a merge kernel (a result then differs from the unsplit
+ *                  one by the order of its fp32 sums; the split depends only on the
+ *                  lengths and the stream's CUs).  Calls that may run at the same time need different
  *                  workspaces.  Unused without host lengths.
  *
  * Supported: head_dim 128 or 64, num_q_heads / num_kv_heads in {1, 2, 4, 8}.
  * Errors as for paged_attn_decode.
  */
-#define LS_PREFILL_WORKSPACE_BYTES ((size_t)256)
+#define LS_PREFILL_COUNTER_BYTES ((size_t)256)
+#define LS_PREFILL_WORKSPACE_BYTES ((size_t)68157696)   /* counters and 512 partial tiles */
 ls_status paged_attn_prefill(ls_kv_pool *pool, int32_t layer, int32_t num_sessions,
                              int32_t num_q_heads, const void *q, const void *k_new,
                              const void *v_new, const int32_t *cu_new_lens,

@@ -430,9 +430,9 @@ ls_status paged_attn_prefill(ls_kv_pool *pool, int32_t layer, int32_t num_sessio
         return fail(LS_EINVAL, "max_new_len (%d) exceeds total_new_tokens (%d)", max_new_len,
                     total_new_tokens);
     if (!(scale > 0.f) || scale != scale) return fail(LS_EINVAL, "scale must be a positive number");
-    if (workspace && workspace_bytes < LS_PREFILL_WORKSPACE_BYTES)
+    if (workspace && workspace_bytes < LS_PREFILL_COUNTER_BYTES)
         return fail(LS_ENOMEM, "prefill workspace of %zu bytes, %zu needed", workspace_bytes,
-                    LS_PREFILL_WORKSPACE_BYTES);
+                    LS_PREFILL_COUNTER_BYTES);
     if (reinterpret_cast<uintptr_t>(workspace) % 16)
         return fail(LS_EINVAL, "prefill workspace must be 16-byte aligned");
     if (lens_host)
@@ -445,14 +445,14 @@ ls_status paged_attn_prefill(ls_kv_pool *pool, int32_t layer, int32_t num_sessio
         hipError_t e = launch_append_prefill(p, layer, num_sessions, total_new_tokens, max_new_len,
                                              static_cast<const uint16_t *>(k_new),
                                              static_cast<const uint16_t *>(v_new), cu_new_lens,
-                                             reused_lens, block_tables, max_blocks_per_session, err,
-                                             stream);
+                                             reused_lens, block_tables, max_blocks_per_session,
+                                             static_cast<uint32_t *>(workspace), err, stream);
         if (e != hipSuccess) return hip_fail(e, "append launch");
     }
     hipError_t e = launch_prefill(p, layer, num_sessions, num_q_heads, static_cast<const uint16_t *>(q),
                                   cu_new_lens, reused_lens, lens_host, total_new_tokens, max_new_len, block_tables,
                                   max_blocks_per_session, scale, static_cast<uint16_t *>(out),
-                                  static_cast<uint32_t *>(workspace), err, stream);
+                                  workspace, workspace_bytes, k_new != nullptr, err, stream);
     return e == hipSuccess ? LS_OK : hip_fail(e, "prefill launch");
 }
 

@@ -56,9 +56,18 @@ struct DecodePlan {
 DecodePlan plan_decode(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads,
                        int32_t max_blocks_per_session);
 
-// Zeroes n (<= 64) 32-bit counters on the stream with a one-wave kernel (not
-// a memset, so that the call can be captured in a graph).
-hipError_t launch_clear_counters(uint32_t *counters, int n, hipStream_t stream);
+// Most pieces of split query tiles in one prefill call: two waves of one piece per
+// CU.  LS_PREFILL_WORKSPACE_BYTES holds the counters and this many pieces of 256
+// rows (maximum, sum and 128 dims in fp32).
+constexpr int kPrefillSplitPieces = 512;
+static_assert(LS_PREFILL_WORKSPACE_BYTES ==
+                  LS_PREFILL_COUNTER_BYTES + (size_t)kPrefillSplitPieces * 256 * (2 + 128) * sizeof(float),
+              "the prefill workspace holds every piece");
+
+// Item counters of a prefill call, one per XCD, at the start of its workspace.
+// They are cleared by a kernel (not a memset, so that the call can be captured
+// in a graph): the append's when the call appends, else one of their own.
+constexpr int kPrefillCounters = 8;
 
 // Kernel launchers (each returns the hipError_t of its launch).
 // Copies the slabs of layers [layer_begin, layer_begin + layer_count) of blocks
@@ -69,11 +78,12 @@ hipError_t launch_block_copy(const PoolGeom &p, int32_t n, const int32_t *ids, u
                              int32_t layer_begin, int32_t layer_count, int32_t stage_block_slabs,
                              int32_t stage_layer0, bool to_pool, double max_gbps,
                              unsigned int *err, hipStream_t stream);
+// counters: prefill item counters to clear, or null.
 hipError_t launch_append_prefill(const PoolGeom &p, int layer, int32_t num_sessions, int32_t total_tokens,
                                  int32_t max_new_len, const uint16_t *k_new, const uint16_t *v_new,
                                  const int32_t *cu_new_lens, const int32_t *reused_lens,
-                                 const int32_t *block_tables, int32_t max_blocks, unsigned int *err,
-                                 hipStream_t stream);
+                                 const int32_t *block_tables, int32_t max_blocks, uint32_t *counters,
+                                 unsigned int *err, hipStream_t stream);
 // With k_new / v_new (both non-null) the step's own token is attended from
 // them and written to its pool slot by the decode kernel itself.
 // The schedule paged_attn_decode runs for a batch: tokens per split, planned
@@ -99,7 +109,8 @@ hipError_t launch_prefill(const PoolGeom &p, int layer, int32_t num_sessions, in
                           const uint16_t *q, const int32_t *cu_new_lens,
                           const int32_t *reused_lens, const int32_t *lens_host, int32_t total_tokens,
                           int32_t max_new_len, const int32_t *block_tables, int32_t max_blocks,
-                          float scale, uint16_t *out, uint32_t *queue, unsigned int *err, hipStream_t stream);
+                          float scale, uint16_t *out, void *workspace, size_t workspace_bytes, bool counters_cleared,
+                          unsigned int *err, hipStream_t stream);
 
 // ---------------------------------------------------------------------------
 // Device helpers

@@ -73,9 +73,11 @@ constexpr int kKeyTile = 64;             // keys per pipeline stage (4 blocks)
 constexpr int kBufferDword3P = 0x00020000;   // raw buffer, 32-bit data format
 constexpr float kLog2eP = 1.4426950408889634f;
 constexpr float kSumLimit = 65536.0f;    // per-lane sum of a unit's P above which m' is raised
-constexpr int kXcds = 8;                 // workgroups are dispatched round-robin over XCDs
+constexpr int kXcds = kPrefillCounters;                 // workgroups are dispatched round-robin over XCDs
 constexpr int kMaxPairs = 512;           // (session, KV head) pairs scheduled; more run in index order
-constexpr int kPlanPairs = 256;          // pairs (and sessions) a host-dealt schedule holds
+constexpr int kPlanPairs = 256;          // entries (and pairs, and sessions) a host-dealt schedule holds
+constexpr int kSplitItems = kPrefillSplitPieces / 2;   // query tiles that can be split (two pieces at least)
+constexpr float kNoKey = -INFINITY;      // a piece's running max for a row that sees none of its keys
 
 struct PrefillArgs {
     const uint16_t *pool;          // layer base
@@ -94,6 +96,8 @@ struct PrefillArgs {
     float scale_log2;
     unsigned int *err;
     uint32_t *queue;               // per-XCD item counters (resident workgroups), or null
+    float *part_ml;                // split query tiles: [piece][row][2] running max (log2 units), row sum
+    float *part_o;                 // [piece][wave][row tile][dim tile][lane][4] unnormalised output
 };
 
 // Schedule dealt on the host when the caller passes the lengths there: every
@@ -106,11 +110,30 @@ struct PrefillHostPlan {
     uint32_t before[kPlanPairs];         // items of the XCD's entries before this one
     uint32_t total[kXcds];               // items of XCD x
 };
+// The same for a call that splits the keys of some query tiles: an entry is a
+// run of query tiles of a pair, over all their keys (chunks == 1) or over one
+// of `chunks` equal parts of them.  An item of a part is a piece: it leaves its
+// running max, row sums and unnormalised output in the workspace, and
+// prefill_merge_kernel adds up a tile's pieces.
+struct PrefillSplitPlan : PrefillHostPlan {
+    uint16_t first_tile[kPlanPairs];     // the entry's first query tile
+    uint16_t piece[kPlanPairs];          // the first query tile's chunk-0 piece (chunks > 1)
+    uint8_t chunk[kPlanPairs];           // the part of the keys this entry covers ...
+    uint8_t chunks[kPlanPairs];          // ... of this many
+};
+// The split query tiles, for the merge.
+struct PrefillSplitTile {
+    uint16_t pair, tile, piece, chunks;  // pieces piece .. piece + chunks - 1
+};
+struct PrefillMergePlan {
+    PrefillSplitTile tile[kSplitItems];
+};
 struct PrefillNoPlan {
     int32_t unused;
 };
-template <bool kHost>
-using PrefillPlanArg = typename std::conditional<kHost, PrefillHostPlan, PrefillNoPlan>::type;
+template <bool kHost, bool kSplit>
+using PrefillPlanArg = typename std::conditional<
+    kSplit, PrefillSplitPlan, typename std::conditional<kHost, PrefillHostPlan, PrefillNoPlan>::type>::type;
 
 // NaN-propagating maxima (v_maximum3_f32 on gfx950: no operand canonicalisation).
 __device__ __forceinline__ float fmax3(float a, float b, float c) {
@@ -136,6 +159,9 @@ __device__ __forceinline__ float xsum16_32(float x) {
     const auto b = __builtin_amdgcn_permlane16_swap(w, w, false, false);
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
+
+// First key tile of part k of `parts` equal parts of ntiles key tiles.
+__device__ __forceinline__ int key_chunk(int ntiles, int k, int parts) { return (int)((unsigned)ntiles * (unsigned)k / (unsigned)parts); }
 
 // Entry jb of a session's block table, or -1 outside [0, nv).  The table does
 // not change during a launch, so it is read through the constant address
@@ -225,8 +251,11 @@ __device__ __forceinline__ void order_phase() {
     }
 }
 
-template <int D, bool kHost>
-__global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, PrefillPlanArg<kHost> plan) {
+// kHost: the schedule comes with the arguments; kSplit: some of its items are
+// parts of a query tile's keys.  (The calls that split nothing keep a kernel
+// without that code: it costs the D = 128 loop two spilled registers.)
+template <int D, bool kHost, bool kSplit = false>
+__global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, PrefillPlanArg<kHost, kSplit> plan) {
     using C = Geo<D>;
     constexpr int KS = D / 32;           // 32-dim k-steps of QK
     constexpr int NDT = D / 16;          // 16-dim output tiles
@@ -253,22 +282,36 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
     const int QT = a.qtiles;
     const int Hkv = a.num_kv_heads;
 
-    // ---- one item: rows of query tile qt of session s, KV head g.
-    auto run_item = [&](const int s, const int g, const int qt) {
+    // ---- one item: rows of query tile qt of session s, KV head g, over part
+    // `chunk` of `chunks` of its keys (chunks > 1: the result goes to piece
+    // `piece` of the workspace).
+    auto run_item = [&](const int s, const int g, const int qt, const int chunk, const int chunks, const int piece) {
         const int n = a.cu[s + 1] - a.cu[s];
         const int j0 = qt * qtok;
         if (j0 >= n || a.cu[s] < 0 || a.cu[s + 1] > a.total) return;   // (lengths outside q: flagged above)
         const int c = a.ctx[s];
         const int j_last = min(j0 + qtok, n) - 1;
-        const int kv_len = c + n;
-        int nblk_valid = (kv_len + kBlock - 1) / kBlock;
+        int nblk_valid = (c + n + kBlock - 1) / kBlock;
         if (nblk_valid > a.max_blocks) {
             nblk_valid = a.max_blocks;
             if (tid == 0) flag_error(a.err, LS_DEVERR_LENGTH);
         }
         const int kv_end = c + j_last + 1;                    // keys this tile can see
-        const int ntiles = (kv_end + kKeyTile - 1) / kKeyTile;
-        const int nb = min(nblk_valid, ntiles * 4);           // blocks any row here can see
+        // This item's key tiles: [tile0, tile0 + ntiles).  Below, keys, blocks
+        // and key tiles are counted from tile0.
+        int tile0 = 0, ntiles = (kv_end + kKeyTile - 1) / kKeyTile;
+        if (kSplit && chunks > 1) {
+            tile0 = key_chunk(ntiles, chunk, chunks);
+            ntiles = key_chunk(ntiles, chunk + 1, chunks) - tile0;
+        }
+        const int key_base = tile0 * kKeyTile;
+        const int kv_len = c + n - key_base;
+        const int nb = min(nblk_valid - tile0 * 4, ntiles * 4);   // blocks any row here can see (none: <= 0)
+
+        if (kSplit && chunks > 1 && ntiles <= 0) {             // a piece without keys
+            for (int r = tid; r < kPreRows; r += kPreThreads) a.part_ml[((int64_t)piece * kPreRows + r) * 2] = kNoKey;
+            return;
+        }
 
         const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
         const int lane = tid % kWave;
@@ -288,7 +331,7 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
             const int h = r % G;
             row_ok[rt] = jl < n;
             const int jc = min(jl, n - 1);
-            row_lim[rt] = c + jc;
+            row_lim[rt] = c + jc - key_base;
             const int64_t tok = (int64_t)a.cu[s] + jc;
             row_out[rt] = (tok * hq_total + g * G + h) * D;
             const uint16_t *qrow = a.q + row_out[rt];
@@ -300,7 +343,7 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
         // wait for q remains inside the key loop (vmcnt(0), other counters untouched).
         __builtin_amdgcn_s_waitcnt(0x0F70);
         // smallest causal limit among this wave's rows: units past it need masking
-        const int wave_lim_min = c + min(j0 + (wave * kWaveRows) / G, n - 1);
+        const int wave_lim_min = c + min(j0 + (wave * kWaveRows) / G, n - 1) - key_base;
 
         // ---- this wave's share of every stage: kLoadsK kilobytes of one K block
         // and of one V block (block 'blk' of the stage), at fixed lane offsets.
@@ -318,7 +361,7 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
             const int p = q * 64 + lane;
             v_voff[e] = (p % D) * 32 + (p / D) * 16;
         }
-        const int32_t *table = a.block_tables + (int64_t)s * a.max_blocks;
+        const int32_t *table = a.block_tables + (int64_t)s * a.max_blocks + (nb > 0 ? tile0 * 4 : 0);
         const uint32_t slab_elems = (uint32_t)(2 * Hkv * kBlock * D);
         const uint32_t nblocks32 = (uint32_t)min(a.num_blocks, (int64_t)0x7fffffff);
         const uint16_t *kbase = a.pool + (int64_t)g * (kBlock * D);
@@ -565,9 +608,15 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
         qk_mfma(sa);
         read_k(k0);                           // unit 1
         mask_unit(sa, 0);
-        // The first unit's row maxima start the running maxima (every row sees key 0).
+        // The first unit's row maxima start the running maxima.  Every row sees
+        // key 0; in a later part of the keys, a row that does not see the first
+        // key sees none of the part (causal), and keeps a finite maximum so that
+        // its probabilities are 0.
     #pragma unroll
-        for (int rt = 0; rt < kRT; ++rt) nm[rt] = -xmax16_32(lane_max(sa[rt])) * sl2;
+        for (int rt = 0; rt < kRT; ++rt) {
+            nm[rt] = -xmax16_32(lane_max(sa[rt])) * sl2;
+            if (kSplit && row_lim[rt] < 0) nm[rt] = 0.f;
+        }
         scale_unit(sa);
         __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the zeros are written
         asm volatile("" ::: "memory");
@@ -628,6 +677,24 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
             tile(j + 3, k3, v3, v2, k0, k1, v1);
         }
 
+        if (kSplit && chunks > 1) {
+            // ---- a piece: maxima, sums and unnormalised output to the workspace,
+            // whole kilobytes per store.
+            float *ml = a.part_ml + ((int64_t)piece * kPreRows + wave * kWaveRows + c16) * 2;
+            float *po = a.part_o + ((int64_t)piece * kPreWaves + wave) * (kRT * NDT * kWave * 4) + lane * 4;
+    #pragma unroll
+            for (int rt = 0; rt < kRT; ++rt) {
+                const float l = xsum16_32(lsum[rt]);
+                if (g4 == 0) {
+                    ml[rt * 32] = row_lim[rt] < 0 ? kNoKey : -nm[rt];
+                    ml[rt * 32 + 1] = l;
+                }
+    #pragma unroll
+                for (int dt = 0; dt < NDT; ++dt)
+                    *reinterpret_cast<f32x4 *>(po + (rt * NDT + dt) * (kWave * 4)) = o[rt][dt];
+            }
+            return;
+        }
         // ---- normalise and write
     #pragma unroll
         for (int rt = 0; rt < kRT; ++rt) {
@@ -669,20 +736,27 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
             if (nt < 0 || nt > planned * qtok || a.ctx[sp] < 0 || a.cu[sp] < 0 || a.cu[sp + 1] > a.total)
                 flag_error(a.err, LS_DEVERR_LENGTH);
         }
-    int s, g, qt;
+    int s, g, qt, chunk = 0, chunks = 1, piece = 0;
     if constexpr (kHost) {
         // Item `slot` of XCD x's list: the entry of the last pair whose earlier
         // items are at most the slot (entries have items, so 'before' increases;
-        // an XCD has at most kPlanPairs / 8 entries, one per lane).
+        // an XCD has at most kWave entries, one per lane).
         auto lookup = [&](int x, uint32_t slot) {
             const int b = plan.start[x], m = plan.start[x + 1] - b;
             const int ln = tid % kWave;
             const bool passed = ln < m && plan.before[b + min(ln, m - 1)] <= slot;
             const int e = b + __popcll(__ballot(passed)) - 1;
             const uint32_t items = (e + 1 < b + m ? plan.before[e + 1] : plan.total[x]) - plan.before[e];
-            qt = (int)(items - 1 - (slot - plan.before[e]));
+            const int t = (int)(items - 1 - (slot - plan.before[e]));    // tile within the entry
+            qt = t;
             s = plan.pair[e] / Hkv;
             g = plan.pair[e] % Hkv;
+            if constexpr (kSplit) {
+                qt += plan.first_tile[e];
+                chunk = plan.chunk[e];
+                chunks = plan.chunks[e];
+                piece = plan.piece[e] + t * chunks + chunk;
+            }
         };
         // Without counters, workgroup i takes item i / 8 of XCD i % 8.  With
         // them (a.queue), workgroup i takes the next item of XCD i % 8's list
@@ -792,38 +866,198 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
         s = (int)(lg / ((int64_t)QT * Hkv));
     }
 
-    run_item(s, g, qt);
+    run_item(s, g, qt, chunk, chunks, piece);
+}
+
+// Adds up the pieces of the split query tiles.  Wave = one (row tile, dim
+// tile) of the kernel that wrote the pieces, with its lane mapping: a piece is
+// one 1 KiB load.  Latency-bound (a few MB to 64 MB over the whole chip), so
+// every wave requests its first kMergePre pieces and their statistics at once,
+// and the grid has a wave for every kilobyte of output (one turn of 301 tokens,
+// 6 parts: 10.2 us with four dim tiles per wave and two passes over the
+// pieces).
+constexpr int kMergeThreads = 256;
+constexpr int kMergeWaves = kMergeThreads / kWave;
+constexpr int kMergePre = 8;
+template <int D>
+__global__ __launch_bounds__(kMergeThreads) void prefill_merge_kernel(PrefillArgs a, PrefillMergePlan plan) {
+    constexpr int NDT = D / 16;
+    constexpr int kWgPerTile = kPreWaves * kRT * NDT / kMergeWaves;
+    const PrefillSplitTile t = plan.tile[blockIdx.x / kWgPerTile];
+    const int unit = blockIdx.x % kWgPerTile * kMergeWaves + (int)threadIdx.x / kWave;   // (row wave, row tile, dim tile)
+    const int lane = threadIdx.x % kWave;
+    const int c16 = lane & 15, g4 = lane >> 4;
+    const int dt = unit % NDT, r = unit / NDT * 16 + c16;
+    constexpr int kMlStep = kPreRows * 2, kOStep = kPreWaves * kRT * NDT * kWave * 4;
+    const float *ml = a.part_ml + (int64_t)t.piece * kMlStep + r * 2;
+    const float *po = a.part_o + (int64_t)t.piece * kOStep + unit * (kWave * 4) + lane * 4;
+    const int G = a.group, Hkv = a.num_kv_heads;
+    const int s = t.pair / Hkv, g = t.pair % Hkv;
+    const int n = a.cu[s + 1] - a.cu[s], row0 = a.cu[s];
+    const int jl = t.tile * (kPreRows / G) + r / G;
+    if (jl >= n || row0 < 0 || row0 + n > a.total) return;    // past the turn (of a tile past it, no piece was written)
+    const int chunks = t.chunks;
+    float M = kNoKey, L = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < chunks; k0 += kMergePre) {
+        float m[kMergePre], l[kMergePre];
+        f32x4 v[kMergePre];
+#pragma unroll
+        for (int i = 0; i < kMergePre; ++i) {
+            const int k = min(k0 + i, chunks - 1);
+            m[i] = ml[k * kMlStep];
+            l[i] = ml[k * kMlStep + 1];
+            v[i] = *reinterpret_cast<const f32x4 *>(po + (int64_t)k * kOStep);
+        }
+        float Mn = M;
+#pragma unroll
+        for (int i = 0; i < kMergePre; ++i) Mn = __builtin_elementwise_maximum(Mn, m[i]);
+        // Keys seen so far (none: Mn is kNoKey and so are M and every m).
+        const float keep = M != kNoKey ? __builtin_amdgcn_exp2f(M - Mn) : 0.f;
+        L *= keep;
+        acc *= keep;
+#pragma unroll
+        for (int i = 0; i < kMergePre; ++i) {
+            // (An empty piece's sums and output were not written; a row without
+            // keys in a piece has zeros.)
+            const bool seen = k0 + i < chunks && m[i] != kNoKey;
+            const float w = seen ? __builtin_amdgcn_exp2f(m[i] - Mn) : 0.f;
+            L += seen ? w * l[i] : 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += seen ? w * v[i][e] : 0.f;
+        }
+        M = Mn;
+    }
+    const float inv = 1.f / L;
+    uint16_t *orow = a.out + (((int64_t)row0 + jl) * Hkv * G + g * G + r % G) * D + dt * 16 + g4 * 4;
+    *reinterpret_cast<u32x2 *>(orow) =
+        u32x2{pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv)};
 }
 
 }  // namespace
 
 namespace {
 
-// Host dealing of the schedule (the device rule, on exact integer work, with
-// each XCD's pairs then ordered by decreasing item length c + n, so that the
-// items an XCD ends with are short).  Returns false when the batch exceeds the
-// plan's capacity (the device deals the schedule then).
-bool plan_prefill_host(int32_t S, int32_t hkv, int32_t qtok, const int32_t *lens, PrefillHostPlan &plan,
-                       int32_t &max_items) {
-    const int P = S * hkv;
-    if (S > kPlanPairs || P > kPlanPairs) return false;
-    struct Pair {
-        int64_t work, len;
-        int32_t p, items, deal;
+// Which query tiles have their keys split, and into how many parts.
+struct SplitChoice {
+    int64_t whole = 0;         // items (longest first) that keep all their keys
+    int32_t target = 0;        // key tiles per part of the others; 0: nothing is split
+};
+
+// A run of equal query tiles: the items of one (session, KV head) pair.
+struct PrefillPair {
+    int64_t work, len;         // len: keys of the pair's longest tile
+    int32_t p, items, tiles;   // tiles: key tiles of that tile
+};
+
+int32_t key_parts(int32_t tiles, int32_t target) { return (tiles + target - 1) / target; }
+
+// With fewer items than CUs, or a last wave of items that fills few of them,
+// a workgroup's serial pass over its keys decides the call's duration: 40 items
+// (one turn of 301 tokens at 32/4 heads) kept 40 of 256 CUs busy for 198 us.
+// Such items are split into parts of their keys, as many as fill the CUs: that
+// call went from 200 to 61 us, and four turns (268 items of 165-268 key tiles,
+// a second wave of 12) from 505 to 455 us.
+// Estimates, in key tiles of one workgroup (about 1.1 us each at D = 128): an
+// unsplit call lasts as long as its total over the CUs, and at least as w + 1
+// items of the length of the (w C + 1)-th longest, which some CU must run; a
+// split one lasts its whole waves plus m waves of parts and the merge.  The
+// least estimate wins, and must win by kSplitGain.  Batches of many waves stay
+// whole (their last wave is a small share and the queue evens it out).
+constexpr int kMinPartTiles = 16;      // key tiles per part: below, an item's start and the merge cost what a part saves
+constexpr int kMaxParts = 32;
+constexpr int kSplitMaxWaves = 6;      // whole waves from which nothing is split
+constexpr int kItemTiles = 3;          // an item's start-up and drain
+constexpr int kMergeTiles = 6;         // the merge launch ...
+constexpr int kPiecesPerMergeTile = 32;   // ... and one more per so many pieces (written and read back)
+constexpr double kSplitGain = 0.93;
+
+SplitChoice choose_split(const PrefillPair *pr, int np, int64_t cus) {   // pr: longest tile first
+    SplitChoice best;
+    int64_t items = 0, total = 0;
+    for (int i = 0; i < np; ++i) {
+        items += pr[i].items;
+        total += (int64_t)pr[i].items * pr[i].tiles;
+    }
+    if (!items || items >= kSplitMaxWaves * cus) return best;
+    // Tiles of the k-th longest item (from 0).
+    auto item_tiles = [&](int64_t k) {
+        for (int i = 0; i < np; ++i) {
+            if (k < pr[i].items) return (int64_t)pr[i].tiles;
+            k -= pr[i].items;
+        }
+        return (int64_t)0;
     };
-    Pair pr[kPlanPairs];
-    int np = 0;
+    double whole_est = (double)total / cus;
+    for (int64_t w = 0; w * cus < items; ++w)
+        whole_est = std::max(whole_est, (double)((w + 1) * (item_tiles(w * cus) + kItemTiles)));
+    double best_est = whole_est * kSplitGain;
+    for (int64_t w = items / cus; w >= 0 && w >= items / cus - 1; --w) {
+        // Pieces of the items past the first w * cus, and their tiles, at a part length.
+        auto pieces_at = [&](int32_t target, int64_t &split_tiles, int64_t &split_items) {
+            int64_t skip = w * cus, pieces = 0;
+            split_tiles = split_items = 0;
+            for (int i = 0; i < np; ++i) {
+                const int64_t cnt = std::max<int64_t>(0, pr[i].items - skip);
+                skip = std::max<int64_t>(0, skip - pr[i].items);
+                if (!cnt) continue;
+                const int32_t parts = key_parts(pr[i].tiles, target);
+                pieces += cnt * parts;
+                if (parts > 1) split_items += cnt;
+                split_tiles += cnt * pr[i].tiles;
+            }
+            return pieces;
+        };
+        const int64_t longest = item_tiles(w * cus);
+        for (int m = 1; m <= 2; ++m) {
+            int32_t lo = (int32_t)std::max<int64_t>(kMinPartTiles, (longest + kMaxParts - 1) / kMaxParts);
+            int32_t hi = (int32_t)longest - 1;
+            int64_t st, si;
+            if (lo > hi || pieces_at(hi, st, si) > m * cus) continue;
+            while (lo < hi) {                       // the least part length that fits m waves
+                const int32_t mid = lo + (hi - lo) / 2;
+                if (pieces_at(mid, st, si) <= m * cus) hi = mid; else lo = mid + 1;
+            }
+            const int64_t pieces = pieces_at(hi, st, si);
+            if (pieces > kPrefillSplitPieces || si > kSplitItems || !si) continue;
+            const double est = (double)(total - st) / cus + (double)(w * kItemTiles) + (double)m * (hi + kItemTiles) +
+                               kMergeTiles + (double)pieces / kPiecesPerMergeTile;
+            if (est < best_est) {
+                best_est = est;
+                best.whole = w * cus;
+                best.target = hi;
+            }
+        }
+    }
+    return best;
+}
+
+// The pairs of the batch in session order; false when the batch exceeds the
+// plan's capacity (the device deals the schedule then).
+bool collect_pairs(int32_t S, int32_t hkv, int32_t qtok, const int32_t *lens, PrefillHostPlan &plan, PrefillPair *pr,
+                   int &np) {
+    if (S > kPlanPairs || S * hkv > kPlanPairs) return false;
+    np = 0;
     for (int s = 0; s < S; ++s) {
         const int32_t n = lens[2 * s], c = lens[2 * s + 1];
         const int32_t items = (int32_t)(((int64_t)n + qtok - 1) / qtok);
         if (items > 0xFFFF) return false;                  // beyond the plan's 16-bit counts
         plan.session_items[s] = (uint16_t)items;
         if (items == 0) continue;
+        const int64_t len = (int64_t)c + n;
         for (int g = 0; g < hkv; ++g)
-            pr[np++] = Pair{(int64_t)items * (2 * (int64_t)c + n), (int64_t)c + n, s * hkv + g, items, 0};
+            pr[np++] = PrefillPair{(int64_t)items * (2 * (int64_t)c + n), len, s * hkv + g, items,
+                                   (int32_t)((len + kKeyTile - 1) / kKeyTile)};
     }
     for (int s = S; s < kPlanPairs; ++s) plan.session_items[s] = 0;
-    std::stable_sort(pr, pr + np, [](const Pair &x, const Pair &y) { return x.work > y.work; });
+    return true;
+}
+
+// Host dealing of an unsplit schedule (the device rule, on exact integer work,
+// with each XCD's pairs then ordered by decreasing item length c + n, so that
+// the items an XCD ends with are short).
+void plan_prefill_host(PrefillPair *pr, int np, PrefillHostPlan &plan, int32_t &max_items) {
+    std::stable_sort(pr, pr + np, [](const PrefillPair &x, const PrefillPair &y) { return x.work > y.work; });
     // Rounds of 8: the round's k-th heaviest pair to the XCD with the k-th least work so far.
     int64_t load[kXcds] = {};
     int xcd_of[kPlanPairs];
@@ -833,7 +1067,6 @@ bool plan_prefill_host(int32_t S, int32_t hkv, int32_t qtok, const int32_t *lens
         std::stable_sort(rank, rank + kXcds, [&](int x, int y) { return load[x] < load[y]; });
         for (int k = 0; k < kXcds && r0 + k < np; ++k) {
             xcd_of[r0 + k] = rank[k];
-            pr[r0 + k].deal = r0 + k;
             load[rank[k]] += pr[r0 + k].work;
         }
     }
@@ -858,25 +1091,115 @@ bool plan_prefill_host(int32_t S, int32_t hkv, int32_t qtok, const int32_t *lens
         max_items = std::max(max_items, (int32_t)acc);
     }
     plan.start[kXcds] = (uint16_t)e;
-    return (int64_t)max_items * kXcds <= 0x7FFFFFFF;
+}
+
+// Host dealing of a split schedule, or false: nothing to split, or more
+// entries, tiles or pieces than the plan holds.  The whole items, longest
+// first, go to the XCDs in runs of one per CU, so that no XCD has a second long
+// item while another's CUs have none (dealing whole pairs here, of 10 to 27
+// items, left some XCDs with 40 items for 32 CUs: 587 us for four turns
+// instead of 500 unsplit); the parts, longest first, each to the XCD with the
+// least work so far.
+bool plan_prefill_split(PrefillPair *pr, int np, int64_t cus, PrefillSplitPlan &plan, PrefillMergePlan &merge,
+                        int32_t &split_tiles, int64_t &items) {
+    std::stable_sort(pr, pr + np, [](const PrefillPair &x, const PrefillPair &y) { return x.len > y.len; });
+    const SplitChoice split = choose_split(pr, np, cus);
+    if (!split.target) return false;
+    struct Entry {
+        int64_t len;
+        int32_t p, items, first, chunk, chunks, piece, xcd;
+    };
+    Entry en[kPlanPairs];
+    int ne = 0;
+    int64_t load[kXcds] = {};
+    int count[kXcds] = {};
+    auto add = [&](const Entry &x) -> bool {
+        if (ne == kPlanPairs || count[x.xcd] == kWave) return false;
+        en[ne++] = x;
+        ++count[x.xcd];
+        load[x.xcd] += x.len * x.items;
+        return true;
+    };
+    const int64_t run = std::max<int64_t>(1, cus / kXcds);
+    int64_t whole = split.whole, dealt = 0;
+    int32_t pieces = 0;
+    split_tiles = 0;
+    struct Rest {
+        int pair;
+        int32_t tiles, parts, piece;
+    };
+    Rest rest[kPlanPairs];
+    int nr = 0;
+    for (int i = 0; i < np; ++i) {
+        const int32_t keep = (int32_t)std::min<int64_t>(whole, pr[i].items);
+        whole -= keep;
+        // Whole items: the pair's last query tiles.
+        for (int32_t t = 0; t < keep;) {
+            const int32_t cnt = (int32_t)std::min<int64_t>(keep - t, run - dealt % run);
+            const int64_t r = dealt / run;                  // runs go 0 .. 7, then 7 .. 0
+            const int x = (int)((r / kXcds) & 1 ? kXcds - 1 - r % kXcds : r % kXcds);
+            if (!add(Entry{pr[i].len, pr[i].p, cnt, pr[i].items - t - cnt, 0, 1, 0, x})) return false;
+            t += cnt;
+            dealt += cnt;
+        }
+        const int32_t left = pr[i].items - keep;
+        if (!left) continue;
+        const int32_t parts = key_parts(pr[i].tiles, split.target);
+        rest[nr++] = Rest{i, left, parts, pieces};
+        if (parts == 1) continue;
+        if (split_tiles + left > kSplitItems || pieces + left * parts > kPrefillSplitPieces) return false;
+        for (int32_t t = 0; t < left; ++t)
+            merge.tile[split_tiles++] =
+                PrefillSplitTile{(uint16_t)pr[i].p, (uint16_t)t, (uint16_t)(pieces + t * parts), (uint16_t)parts};
+        pieces += left * parts;
+    }
+    if (!split_tiles) return false;
+    std::stable_sort(rest, rest + nr, [&](const Rest &x, const Rest &y) {
+        return pr[x.pair].len / x.parts > pr[y.pair].len / y.parts;
+    });
+    for (int i = 0; i < nr; ++i)
+        for (int32_t k = 0; k < rest[i].parts; ++k) {
+            int x = 0;
+            for (int y = 1; y < kXcds; ++y)
+                if (load[y] < load[x]) x = y;
+            const PrefillPair &q = pr[rest[i].pair];
+            if (!add(Entry{q.len / rest[i].parts, q.p, rest[i].tiles, 0, k, rest[i].parts, rest[i].piece, x})) return false;
+        }
+    // Per XCD, entries by decreasing item length (ties in dealing order).
+    std::stable_sort(en, en + ne, [](const Entry &x, const Entry &y) { return x.xcd != y.xcd ? x.xcd < y.xcd : x.len > y.len; });
+    items = 0;
+    int e = 0;
+    for (int x = 0; x < kXcds; ++x) {
+        plan.start[x] = (uint16_t)e;
+        uint32_t acc = 0;
+        for (; e < ne && en[e].xcd == x; ++e) {
+            plan.pair[e] = (uint16_t)en[e].p;
+            plan.before[e] = acc;
+            plan.first_tile[e] = (uint16_t)en[e].first;
+            plan.piece[e] = (uint16_t)en[e].piece;
+            plan.chunk[e] = (uint8_t)en[e].chunk;
+            plan.chunks[e] = (uint8_t)en[e].chunks;
+            acc += (uint32_t)en[e].items;
+        }
+        plan.total[x] = acc;
+        items += acc;
+    }
+    plan.start[kXcds] = (uint16_t)e;
+    return true;
 }
 
 }  // namespace
 
-__global__ void clear_counters_kernel(uint32_t *counters, int n) {
-    if ((int)threadIdx.x < n) counters[threadIdx.x] = 0u;
-}
-
-hipError_t launch_clear_counters(uint32_t *counters, int n, hipStream_t stream) {
-    hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(kWave), 0, stream, counters, n);
-    return hipGetLastError();
+__global__ void clear_counters_kernel(uint32_t *counters) {
+    if ((int)threadIdx.x < kPrefillCounters) counters[threadIdx.x] = 0u;
 }
 
 hipError_t launch_prefill(const PoolGeom &p, int layer, int32_t num_sessions, int32_t num_q_heads,
                           const uint16_t *q, const int32_t *cu_new_lens,
                           const int32_t *reused_lens, const int32_t *lens_host, int32_t total_tokens,
                           int32_t max_new_len, const int32_t *block_tables, int32_t max_blocks,
-                          float scale, uint16_t *out, uint32_t *queue, unsigned int *err, hipStream_t stream) {
+                          float scale, uint16_t *out, void *workspace, size_t workspace_bytes, bool counters_cleared,
+                          unsigned int *err, hipStream_t stream) {
     if (num_sessions <= 0 || max_new_len <= 0) return hipSuccess;
     PrefillArgs a;
     a.pool = p.layer_base(layer);
@@ -894,27 +1217,65 @@ hipError_t launch_prefill(const PoolGeom &p, int layer, int32_t num_sessions, in
     a.scale_log2 = scale * kLog2eP;
     a.err = err;
     a.queue = nullptr;
+    a.part_ml = nullptr;
+    a.part_o = nullptr;
     const int qtok = kPreRows / a.group;
     a.qtiles = (max_new_len + qtok - 1) / qtok;
-    PrefillHostPlan plan;
-    int32_t max_items = 0;
-    if (lens_host && plan_prefill_host(num_sessions, p.num_kv_heads, qtok, lens_host, plan, max_items)) {
-        if (max_items == 0) return hipSuccess;
-        dim3 grid((unsigned)(kXcds * max_items));
-        if (queue) {
-            // Items are taken through the counters; ~10% more workgroups than
-            // items let the faster XCDs take over the slower ones' last items.
-            if (hipError_t e = launch_clear_counters(queue, kXcds, stream)) return e;
-            a.queue = queue;
-            int64_t items = 0;
-            for (int x = 0; x < kXcds; ++x) items += plan.total[x];
+    PrefillSplitPlan plan;
+    PrefillPair pairs_of[kPlanPairs];
+    int np = 0;
+    if (lens_host && collect_pairs(num_sessions, p.num_kv_heads, qtok, lens_host, plan, pairs_of, np)) {
+        if (np == 0) return hipSuccess;
+        // Items are taken through the counters of a workspace; ~10% more
+        // workgroups than items let the faster XCDs take over the slower ones'
+        // last items.
+        auto queue_grid = [&](int64_t items) {
             const int64_t per_xcd = (items + kXcds - 1) / kXcds + (items + 10 * kXcds - 1) / (10 * kXcds);
-            grid = dim3((unsigned)(kXcds * per_xcd));
+            return dim3((unsigned)(kXcds * per_xcd));
+        };
+        if (workspace) {
+            a.queue = static_cast<uint32_t *>(workspace);
+            if (!counters_cleared) {
+                hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(kWave), 0, stream, a.queue);
+                if (hipError_t e = hipGetLastError()) return e;
+            }
         }
+        // Splitting needs the counters (items of many lengths) and room for the pieces.
+        PrefillMergePlan merge;
+        int32_t split_tiles = 0;
+        int64_t items = 0;
+        if (workspace && workspace_bytes >= LS_PREFILL_WORKSPACE_BYTES &&
+            plan_prefill_split(pairs_of, np, stream_cus(p, stream), plan, merge, split_tiles, items)) {
+            uint8_t *parts = static_cast<uint8_t *>(workspace) + LS_PREFILL_COUNTER_BYTES;
+            a.part_ml = reinterpret_cast<float *>(parts);
+            a.part_o = reinterpret_cast<float *>(parts + (size_t)kPrefillSplitPieces * kPreRows * 2 * sizeof(float));
+            const dim3 grid = queue_grid(items), mgrid((unsigned)(split_tiles * (kPreWaves * kRT * p.head_dim / 16 / kMergeWaves)));
+            if (p.head_dim == 128)
+                hipLaunchKernelGGL((prefill_kernel<128, true, true>), grid, dim3(kPreThreads), 0, stream, a, plan);
+            else
+                hipLaunchKernelGGL((prefill_kernel<64, true, true>), grid, dim3(kPreThreads), 0, stream, a, plan);
+            if (hipError_t e = hipGetLastError()) return e;
+            if (p.head_dim == 128)
+                hipLaunchKernelGGL(prefill_merge_kernel<128>, mgrid, dim3(kMergeThreads), 0, stream, a, merge);
+            else
+                hipLaunchKernelGGL(prefill_merge_kernel<64>, mgrid, dim3(kMergeThreads), 0, stream, a, merge);
+            return hipGetLastError();
+        }
+        // (The split planner may have reordered the pairs: back to session order.)
+        std::sort(pairs_of, pairs_of + np, [](const PrefillPair &x, const PrefillPair &y) { return x.p < y.p; });
+        int32_t max_items = 0;
+        plan_prefill_host(pairs_of, np, plan, max_items);
+        dim3 grid((unsigned)(kXcds * max_items));
+        if (workspace) {
+            int64_t total = 0;
+            for (int x = 0; x < kXcds; ++x) total += plan.total[x];
+            grid = queue_grid(total);
+        }
+        const PrefillHostPlan &whole = plan;
         if (p.head_dim == 128)
-            hipLaunchKernelGGL((prefill_kernel<128, true>), grid, dim3(kPreThreads), 0, stream, a, plan);
+            hipLaunchKernelGGL((prefill_kernel<128, true>), grid, dim3(kPreThreads), 0, stream, a, whole);
         else
-            hipLaunchKernelGGL((prefill_kernel<64, true>), grid, dim3(kPreThreads), 0, stream, a, plan);
+            hipLaunchKernelGGL((prefill_kernel<64, true>), grid, dim3(kPreThreads), 0, stream, a, whole);
         return hipGetLastError();
     }
     // An XCD holds at most ceil(pairs / 8) pairs of at most qtiles items each;

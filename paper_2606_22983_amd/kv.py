@@ -65,7 +65,8 @@ for _f in (_lib.kv_pool_create, _lib.kv_pool_destroy, _lib.paged_attn_decode,
 
 LS_OK, LS_EINVAL, LS_ENOMEM, LS_EHIP, LS_EUNSUPPORTED = 0, -22, -12, -5, -95
 LS_DEVERR_BLOCK_ID, LS_DEVERR_LENGTH, LS_DEVERR_INTERNAL = 0x1, 0x2, 0x4
-PREFILL_WORKSPACE_BYTES = 256     # LS_PREFILL_WORKSPACE_BYTES
+PREFILL_COUNTER_BYTES = 256            # LS_PREFILL_COUNTER_BYTES
+PREFILL_WORKSPACE_BYTES = 68157696     # LS_PREFILL_WORKSPACE_BYTES
 
 
 class LiveServeError(RuntimeError):
@@ -268,8 +269,9 @@ def paged_attn_prefill(pool: KVPool, layer: int, q: torch.Tensor, cu_new_lens: t
     """q/out: [T][Hq][D] bf16; cu_new_lens int32 [S+1]; reused_lens int32 [S];
     k_new/v_new [T][Hkv][D] bf16; lens_host: optional host [S][2] of (n_s, c_s);
     workspace: optional device tensor of PREFILL_WORKSPACE_BYTES bytes (item
-    counters that let faster XCDs take over the slower ones' last tiles; used
-    with lens_host)."""
+    counters that let faster XCDs take over the slower ones' last tiles, and room
+    for partial results when few query tiles have their keys split over the GPU;
+    used with lens_host; PREFILL_COUNTER_BYTES are enough for the counters alone)."""
     if q.dim() != 3:
         raise ValueError("q must be [T][Hq][D]")
     total, hq = q.shape[0], q.shape[1]

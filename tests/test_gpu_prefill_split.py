@@ -1,0 +1,111 @@
+"""Prefill calls whose query tiles are too few to fill the GPU: their keys are split over
+workgroups and merged (host lengths and a full-size workspace).  Against the oracle, where parts
+end at tile edges, inside the causal diagonal or hold no key of a row."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from tests.gpu_util import DevicePool, assert_attn_close, bf16_dev, i32_dev, scale_keys
+from tests.test_gpu_prefill import _case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def kv():
+    from paper_2606_22983_amd import kv as kv_mod
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return kv_mod
+
+
+def _call(kv, dp, q, kn, vn, n, c, tables, d, ws_bytes, lens_dev=None):
+    n_dev, c_dev = (n, c) if lens_dev is None else lens_dev
+    cu = np.concatenate([[0], np.cumsum(n_dev)]).astype(np.int32)
+    out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((ws_bytes,), 0xFF, dtype=torch.uint8, device="cuda")       # NaN partials, garbage counters
+    kv.paged_attn_prefill(dp.pool, 0, bf16_dev(q), i32_dev(cu), i32_dev(c_dev), int(np.max(n)), i32_dev(tables),
+                          1 / math.sqrt(d), out, None if kn is None else bf16_dev(kn),
+                          None if vn is None else bf16_dev(vn), lens_host=np.stack([n, c], 1), workspace=ws)
+    # The pieces' region (256 rows of maximum and sum) is written exactly when something was split.
+    split = not bool((ws[kv.PREFILL_COUNTER_BYTES:] == 0xFF).all())
+    return out, cu, split
+
+
+# (hq, hkv, d, n, c): one short turn over a long context (many parts); a first turn whose parts end
+# inside the causal diagonal; one new token; lengths one past a key tile; several uneven turns with
+# an empty one; one query head per KV head; a second wave of which only a remainder is split.
+@pytest.mark.parametrize("hq,hkv,d,n,c", [
+    (32, 4, 128, [301], [9043]), (4, 1, 128, [2048], [0]), (8, 1, 128, [1], [16384]), (8, 2, 64, [65], [4097]),
+    (16, 2, 128, [33, 0, 257, 8], [5000, 7000, 3001, 12]), (8, 8, 64, [700], [2000]), (4, 4, 128, [256, 255], [2047, 3000]),
+    (32, 4, 128, [560, 560, 560, 560], [6300, 6100, 6049, 5500])])
+def test_split_prefill_matches_oracle(kv, oracle_lib, hq, hkv, d, n, c):
+    rng = np.random.default_rng(hq * 7 + n[0])
+    n, c = np.array(n), np.array(c)
+    pool, tables, q, kn, vn = _case(rng, n, c, hq, hkv, d)
+    dp = DevicePool(kv, pool, d)
+    out, cu, split = _call(kv, dp, q, kn, vn, n, c, tables, d, kv.PREFILL_WORKSPACE_BYTES)
+    ref, ref_pool = oracle_lib.prefill(pool, 16, d, 0, q, kn, vn, cu, c, tables, 1 / math.sqrt(d), pool_out=True)
+    assert split
+    assert_attn_close(out, ref, "split prefill n=%s c=%s" % (n, c))
+    assert np.array_equal(dp.host(), ref_pool)
+    # Without an append (the K/V is in the pool now) the counters are cleared by their own kernel.
+    again, _, _ = _call(kv, dp, q, None, None, n, c, tables, d, kv.PREFILL_WORKSPACE_BYTES)
+    assert torch.equal(out.view(torch.int16), again.view(torch.int16))
+    # A counters-only workspace is still taken, and splits nothing.
+    whole, _, split = _call(kv, dp, q, None, None, n, c, tables, d, kv.PREFILL_COUNTER_BYTES)
+    assert not split
+    assert_attn_close(whole, ref, "unsplit prefill n=%s c=%s" % (n, c))
+    assert kv.ls_device_errors() == 0
+
+
+@pytest.mark.parametrize("shape", ["rising", "spike", "falling"])
+def test_split_prefill_of_peaky_scores(kv, oracle_lib, shape):
+    """Parts whose maxima differ by orders of magnitude."""
+    rng = np.random.default_rng(5)
+    n, c, d = np.array([40]), np.array([6000]), 128
+    pool, tables, q, kn, vn = _case(rng, n, c, 16, 2, d)
+    scale_keys(pool, tables, c, shape)
+    dp = DevicePool(kv, pool, d)
+    out, cu, split = _call(kv, dp, q, kn, vn, n, c, tables, d, kv.PREFILL_WORKSPACE_BYTES)
+    assert split
+    assert_attn_close(out, oracle_lib.prefill(pool, 16, d, 0, q, kn, vn, cu, c, tables, 1 / math.sqrt(d)), shape)
+
+
+def test_split_prefill_with_other_device_lengths(kv, oracle_lib):
+    """The plan is the host's, the lengths are the device's: a shorter device turn and context (all
+    its tiles, and parts, shrink) give the device lengths' result."""
+    rng = np.random.default_rng(6)
+    n, c, d = np.array([200]), np.array([5000]), 128
+    pool, tables, q, kn, vn = _case(rng, n, c, 16, 2, d)
+    dp = DevicePool(kv, pool, d)
+    dn, dc = np.array([70]), np.array([100])
+    out, cu, split = _call(kv, dp, q, kn, vn, n, c, tables, d, kv.PREFILL_WORKSPACE_BYTES, lens_dev=(dn, dc))
+    assert split
+    ref = oracle_lib.prefill(pool, 16, d, 0, q[:70], kn[:70], vn[:70], cu, dc, tables, 1 / math.sqrt(d))
+    assert_attn_close(out[:70], ref, "shorter device lengths")
+    assert bool(torch.isnan(out[70:]).all())                  # rows past the turn are not written
+    kv.ls_device_errors()
+
+
+def test_split_prefill_replays_from_a_graph(kv):
+    rng = np.random.default_rng(8)
+    n, c, d, hq, hkv = np.array([100]), np.array([8000]), 128, 32, 4
+    pool, tables, q, kn, vn = _case(rng, n, c, hq, hkv, d)
+    dp = DevicePool(kv, pool, d)
+    eager, cu, split = _call(kv, dp, q, kn, vn, n, c, tables, d, kv.PREFILL_WORKSPACE_BYTES)
+    assert split
+    ws = torch.empty(kv.PREFILL_WORKSPACE_BYTES, dtype=torch.uint8, device="cuda")
+    args = [bf16_dev(q), i32_dev(cu), i32_dev(c), 100, i32_dev(tables), 1 / math.sqrt(d), torch.empty_like(eager),
+            bf16_dev(kn), bf16_dev(vn)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        kv.paged_attn_prefill(dp.pool, 0, *args, lens_host=np.stack([n, c], 1), workspace=ws)
+    for rep in range(3):
+        ws.fill_(0x77)
+        args[6].fill_(0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(args[6].view(torch.int16), eager.view(torch.int16)), rep
