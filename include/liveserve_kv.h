@@ -109,8 +109,8 @@ ls_status kv_pool_destroy(ls_kv_pool *pool);
 
 /*
  * Workspace bytes paged_attn_decode needs for this shape: the split-K partial
- * results (running max, running sum and unnormalised output per split, fp32).
- * No initialisation is needed; calls on one stream may reuse the same
+ * results (running max, running sum and unnormalised output per split, fp32)
+ * and a small batch's arrival counts.  No initialisation is needed; calls on one stream may reuse the same
  * workspace, concurrent calls need their own.  Returns 0 for invalid arguments.
  */
 size_t ls_decode_workspace_bytes(const ls_kv_pool *pool, int32_t num_sessions,
@@ -144,7 +144,8 @@ size_t ls_decode_workspace_bytes(const ls_kv_pool *pool, int32_t num_sessions,
  *   out            device bf16 [num_sessions][num_q_heads][head_dim]:
  *                  out = softmax(scale * q K^T) V over the session's keys, per query
  *                  head h using KV head h / (num_q_heads / num_kv_heads)
- *   workspace      device, >= ls_decode_workspace_bytes(...) bytes
+ *   workspace      device, >= ls_decode_workspace_bytes(...) bytes, 16-byte aligned for
+ *                  the single-launch schedule of small batches
  *
  * Supported: num_q_heads / num_kv_heads in {1, 2, 4, 8}; at most 2048 sessions
  * and 16384 blocks (262,144 tokens) per session.  Errors: LS_EINVAL
@@ -163,10 +164,11 @@ ls_status paged_attn_decode(ls_kv_pool *pool, int32_t layer, int32_t num_session
  * ls_decode_schedule — how paged_attn_decode will run a batch of this shape
  * on `stream`: *split_tokens tokens per split, *host_planned 1 when the
  * schedule is planned on the host from context_lens_host (0: in the kernel,
- * also when the host plan is estimated to be no faster or has more items than
+ * a small batch's split size from the table's width; also when the host plan is
+ * estimated to be no faster or has more items than
  * the kernel arguments carry: 7680 for batches of at most 1024 sessions, 4 KV
  * heads and 8 splits per session, else 3840), *merge 1 when the split merge
- * kernel runs.  appended: 1
+ * kernel runs (a small batch's splits are merged by its one kernel: 0).  appended: 1
  * when k_new / v_new will be given.  Pure host computation; LS_EINVAL as for
  * paged_attn_decode.
  */

@@ -322,7 +322,7 @@ ls_status kv_pool_destroy(ls_kv_pool *pool) {
 size_t ls_decode_workspace_bytes(const ls_kv_pool *pool, int32_t num_sessions,
                                  int32_t num_q_heads, int32_t max_blocks_per_session) {
     if (!pool || num_sessions <= 0 || max_blocks_per_session <= 0 || num_q_heads <= 0) return 0;
-    return plan_decode(pool->geom, num_sessions, num_q_heads, max_blocks_per_session).total();
+    return plan_decode(pool->geom, num_sessions, num_q_heads, max_blocks_per_session).recommended();
 }
 
 ls_status paged_attn_decode(ls_kv_pool *pool, int32_t layer, int32_t num_sessions,
@@ -360,7 +360,7 @@ ls_status paged_attn_decode(ls_kv_pool *pool, int32_t layer, int32_t num_session
     hipError_t e = launch_decode(p, layer, num_sessions, num_q_heads, static_cast<const uint16_t *>(q),
                                  static_cast<const uint16_t *>(k_new), static_cast<const uint16_t *>(v_new),
                                  block_tables, max_blocks_per_session, context_lens, context_lens_host,
-                                 scale, static_cast<uint16_t *>(out), workspace, plan, err, stream);
+                                 scale, static_cast<uint16_t *>(out), workspace, workspace_bytes, plan, err, stream);
     return e == hipSuccess ? LS_OK : hip_fail(e, "decode launch");
 }
 
@@ -378,7 +378,8 @@ ls_status ls_decode_schedule(const ls_kv_pool *pool, int32_t num_sessions, int32
     if (context_lens_host)
         if (ls_status st = check_decode_lens_host(num_sessions, context_lens_host, appended, max_blocks_per_session))
             return st;
-    const DecodeSchedule sc = decode_schedule(p, num_sessions, context_lens_host, appended, plan, stream);
+    const DecodeSchedule sc = decode_schedule(p, num_sessions, num_q_heads, max_blocks_per_session,
+                                              context_lens_host, appended, plan, stream);
     *split_tokens = sc.split_tokens;
     *host_planned = sc.host_planned ? 1 : 0;
     *merge = sc.merge ? 1 : 0;

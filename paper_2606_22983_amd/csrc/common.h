@@ -44,6 +44,17 @@ int stream_cus(const PoolGeom &p, hipStream_t stream);
 // the runtime could not resolve it.  Kernels receive it as an argument.
 unsigned int *device_error_word();
 
+// A small batch's decode: one workgroup per split, merged by the last of each
+// (session, KV head).  split_tokens 0: the batch is not small.
+struct SmallDecodePlan {
+    int split_tokens = 0;
+    int rows = 0;                   // (session, split) rows (device lengths: their bound)
+    size_t count_bytes = 0;         // uint64 [S][Hkv] arrival counts, 128 bytes apart
+    size_t ml_bytes = 0;            // fp32 [rows][Hkv][G][2]
+    size_t acc_bytes = 0;           // fp32 [rows][Hkv][G][D]
+    size_t total() const { return count_bytes + ml_bytes + acc_bytes; }
+};
+
 // Split-K planning shared by paged_attn_decode and its workspace query.
 struct DecodePlan {
     int split_tokens;               // tokens per split (multiple of 64)
@@ -51,8 +62,14 @@ struct DecodePlan {
     bool supported;                 // false when a session could need too many splits
     size_t ml_bytes;                // fp32 [S][Hkv][max_splits][G][2]
     size_t acc_bytes;               // fp32 [S][Hkv][max_splits][G][D]
-    size_t total() const { return ml_bytes + acc_bytes; }
+    size_t small_bytes;             // what a small batch's kernel may use
+    size_t total() const { return ml_bytes + acc_bytes; }            // the least a call takes
+    size_t recommended() const { return total() > small_bytes ? total() : small_bytes; }
 };
+// lens_host null: every session may be as long as its table.  bytes: room for
+// counts and partials.
+SmallDecodePlan plan_small(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads, int32_t max_blocks,
+                           const int32_t *lens_host, int32_t appended, size_t bytes);
 DecodePlan plan_decode(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads,
                        int32_t max_blocks_per_session);
 
@@ -93,8 +110,9 @@ struct DecodeSchedule {
     bool host_planned;
     bool merge;
 };
-DecodeSchedule decode_schedule(const PoolGeom &p, int32_t num_sessions, const int32_t *context_lens_host,
-                               int32_t appended, const DecodePlan &plan, hipStream_t stream);
+DecodeSchedule decode_schedule(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads, int32_t max_blocks,
+                               const int32_t *context_lens_host, int32_t appended, const DecodePlan &plan,
+                               hipStream_t stream);
 
 // With context_lens_host (the same lengths on the host) the split-K schedule
 // is planned on the host; the split merge is launched only if some session is
@@ -103,8 +121,8 @@ hipError_t launch_decode(const PoolGeom &p, int layer, int32_t num_sessions, int
                          const uint16_t *q, const uint16_t *k_new, const uint16_t *v_new,
                          const int32_t *block_tables,
                          int32_t max_blocks, const int32_t *context_lens, const int32_t *context_lens_host,
-                         float scale, uint16_t *out, void *workspace, const DecodePlan &plan,
-                         unsigned int *err, hipStream_t stream);
+                         float scale, uint16_t *out, void *workspace, size_t workspace_bytes,
+                         const DecodePlan &plan, unsigned int *err, hipStream_t stream);
 hipError_t launch_prefill(const PoolGeom &p, int layer, int32_t num_sessions, int32_t num_q_heads,
                           const uint16_t *q, const int32_t *cu_new_lens,
                           const int32_t *reused_lens, const int32_t *lens_host, int32_t total_tokens,

@@ -39,6 +39,7 @@
 #include <algorithm>
 #include <cstring>
 #include <cstdlib>
+#include <iterator>
 #include <type_traits>
 #include <vector>
 
@@ -93,6 +94,7 @@ struct DecodeArgs {
     float *part_acc;               // [S][Hkv][max_splits][G][D]
     unsigned int *err;             // device error word
     int32_t num_sessions;
+    uint64_t *arrived;             // decode_small_kernel: [S][Hkv] arrival counts (kArrivedTag | count)
 };
 
 // A schedule planned on the host (paged_attn_decode with host lengths),
@@ -183,10 +185,11 @@ __device__ __forceinline__ int attended_len(const DecodeArgs &a, int s, bool may
 }
 
 // Issue the loads of one block (blk < 0: a zero-size descriptor, nothing fetched).
+// koff, voff: this lane's byte offsets in k-step 0 and dim tile 0; the others
+// are constants further, kept in scalar registers.
 template <int D>
 __device__ __forceinline__ void load_block(BlockRegs<D> &r, const uint16_t *pool, int32_t num_kv_heads,
-                                           int32_t g, int32_t blk, const int (&koff)[D / 32],
-                                           const int (&voff)[D / 16]) {
+                                           int32_t g, int32_t blk, int koff, int voff) {
     constexpr int kTileElems = kBlock * D;
     const bool valid = blk >= 0;
     const uint16_t *kt = pool + ((int64_t)(valid ? blk : 0) * 2 * num_kv_heads + g) * kTileElems;
@@ -195,9 +198,9 @@ __device__ __forceinline__ void load_block(BlockRegs<D> &r, const uint16_t *pool
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(kt), 0, bytes, kBufferDword3);
     const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(vt), 0, bytes, kBufferDword3);
 #pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) r.k[ks] = __builtin_amdgcn_raw_buffer_load_b128(rk, koff[ks], 0, kStreamLoad);
+    for (int ks = 0; ks < D / 32; ++ks) r.k[ks] = __builtin_amdgcn_raw_buffer_load_b128(rk, koff, ks * 4 * kBlock * 16, kStreamLoad);
 #pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) r.v[dt] = __builtin_amdgcn_raw_buffer_load_b64(rv, voff[dt], 0, kStreamLoad);
+    for (int dt = 0; dt < D / 16; ++dt) r.v[dt] = __builtin_amdgcn_raw_buffer_load_b64(rv, voff, dt * 16 * kBlock * 2, kStreamLoad);
 }
 
 // Online-softmax update with one 16-token block held in registers.
@@ -249,6 +252,39 @@ __device__ __forceinline__ void process_block(BlockRegs<D> &r, const bf16x8 (&qo
     for (int dt = 0; dt < D / 16; ++dt)
         o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, r.v[dt]), pb,
                                                           o[dt], 0, 0, 0);
+}
+
+// The step's own token (position Lp) of (session s, KV head g): attended as a
+// one-token tile built from k_new / v_new, and written to slot Lp % 16 of its
+// block blk (-1: no such block) for later steps.
+template <int D>
+__device__ __forceinline__ void attend_own(const DecodeArgs &a, int s, int g, int Lp, int blk,
+                                           const bf16x8 (&qop)[D / 32], int g4, int c16, int lane, float &m,
+                                           float &lsum, f32x4 (&o)[D / 16]) {
+    const int64_t row = ((int64_t)s * a.num_kv_heads + g) * D;
+    BlockRegs<D> nr;
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) {
+        const u32x4 kv = *reinterpret_cast<const u32x4 *>(a.k_new + row + ks * 32 + g4 * 8);
+        nr.k[ks] = c16 == 0 ? kv : u32x4{0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt) {
+        const uint32_t v0 = a.v_new[row + dt * 16 + c16];
+        nr.v[dt] = u32x2{g4 == 0 ? v0 : 0u, 0u};
+    }
+    process_block<D>(nr, qop, Lp, Lp + 1, a.scale_log2, g4, m, lsum, o);
+    if (blk >= 0) {
+        const int t = Lp % kBlock;
+        uint16_t *pool = const_cast<uint16_t *>(a.pool);
+        const int64_t tile = (int64_t)kBlock * D;
+        uint16_t *kt = pool + ((int64_t)blk * 2 * a.num_kv_heads + g) * tile;
+        uint16_t *vt = kt + (int64_t)a.num_kv_heads * tile;
+        for (int d = lane; d < D; d += kWave) {
+            kt[((d >> 3) * kBlock + t) * 8 + (d & 7)] = a.k_new[row + d];
+            vt[d * kBlock + t] = a.v_new[row + d];
+        }
+    }
 }
 
 // Block-wide exclusive scan of one value per thread (kDecThreads threads),
@@ -414,11 +450,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeArgs a, PlanA
     const int lane = tid % kWave;
     const int c16 = lane & 15;
     const int g4 = lane >> 4;
-    int koff[D / 32], voff[D / 16];
-#pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) koff[ks] = ((ks * 4 + g4) * kBlock + c16) * 16;   // = ks*1024 + lane*16
-#pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) voff[dt] = ((dt * 16 + c16) * kBlock + g4 * 4) * 2;
+    const int koff = (g4 * kBlock + c16) * 16, voff = (c16 * kBlock + g4 * 4) * 2;
 
     // (session, split) of work row r of the device schedule.  A full row: the
     // largest s with sm_cum[s] <= r (a session without full splits shares its
@@ -594,31 +626,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeArgs a, PlanA
         if (own && cur_split == nsplit - 1 && last_chunk) {
             const int bl = Lp / kBlock - blk0;             // the token's block within the chunk
             if (wave == bl % kDecWaves) {
-                const int64_t row = ((int64_t)cur_s * a.num_kv_heads + cur_g) * D;
-                BlockRegs<D> nr;
-#pragma unroll
-                for (int ks = 0; ks < D / 32; ++ks) {
-                    const u32x4 kv = *reinterpret_cast<const u32x4 *>(a.k_new + row + ks * 32 + g4 * 8);
-                    nr.k[ks] = c16 == 0 ? kv : u32x4{0u, 0u, 0u, 0u};
-                }
-#pragma unroll
-                for (int dt = 0; dt < D / 16; ++dt) {
-                    const uint32_t v0 = a.v_new[row + dt * 16 + c16];
-                    nr.v[dt] = u32x2{g4 == 0 ? v0 : 0u, 0u};
-                }
-                process_block<D>(nr, qop, Lp, Lp + 1, a.scale_log2, g4, m, lsum, o);
-                const int blk = checked_id(cur_ids, bl, nblk);
-                if (blk >= 0) {
-                    const int t = Lp % kBlock;
-                    uint16_t *pool = const_cast<uint16_t *>(a.pool);
-                    const int64_t tile = (int64_t)kBlock * D;
-                    uint16_t *kt = pool + ((int64_t)blk * 2 * a.num_kv_heads + cur_g) * tile;
-                    uint16_t *vt = kt + (int64_t)a.num_kv_heads * tile;
-                    for (int d = lane; d < D; d += kWave) {
-                        kt[((d >> 3) * kBlock + t) * 8 + (d & 7)] = a.k_new[row + d];
-                        vt[d * kBlock + t] = a.v_new[row + d];
-                    }
-                }
+                attend_own<D>(a, cur_s, cur_g, Lp, checked_id(cur_ids, bl, nblk), qop, g4, c16, lane, m, lsum, o);
             }
         }
         // Request the next chunk's first blocks (and a new item's q) before
@@ -708,6 +716,283 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeArgs a, PlanA
                 __hip_atomic_fetch_add(&sm_merged[slot], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
         }
+    }
+}
+
+// Small batches: one workgroup per (row, KV head g), a row being a split of a
+// session; no second launch.  What bounds such a call is a chain of latencies,
+// not bandwidth, so the chain is kept short: block ids, q and the length are
+// requested together, every wave's first blocks right after, and the last
+// split of a (session, KV head) to finish merges them all.  The rows come in
+// the arguments when the host knows the lengths; else every wave finds its row
+// by a scan over the lengths, so that the workgroups without one come last.
+// (A grid of all sessions by the longest one's splits instead, 704 workgroups
+// of which 252 had keys, started its last ones 26 us into the call.)
+//
+// The finishing order is taken from a 64-bit count per (session, KV head) in
+// the workspace, whose contents on entry are arbitrary: a word counts only if
+// its upper 48 bits are the tag.  A split adds 1; if the word it found was
+// tagged, it was the count; otherwise the word is replaced (compare-and-swap)
+// by the tag and a first count, or, when another split has just done so, the
+// add is made again on the tagged word.  The last one leaves tag | 0.  A
+// stray word equal to a tag with a nonzero count cannot be left by a finished
+// call, and by chance has odds of 2^-48 per word.
+constexpr uint64_t kArrivedTag = 0x9D3B6E52C1A70000ull;
+constexpr uint64_t kArrivedMask = 0xFFFFull;
+constexpr int kArrivedStride = 16;           // words from one count to the next: a cache line each
+
+__device__ __forceinline__ unsigned count_arrival(uint64_t *word) {
+    uint64_t old = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while ((old & ~kArrivedMask) != kArrivedTag) {
+        uint64_t cur = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((cur & ~kArrivedMask) == kArrivedTag) {
+            old = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else if (__hip_atomic_compare_exchange_strong(word, &cur, kArrivedTag | 1ull, __ATOMIC_RELAXED,
+                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+            old = kArrivedTag;
+        }
+    }
+    return (unsigned)(old & kArrivedMask);
+}
+
+// Partials and counts cross XCDs, whose L2s are not coherent, so they are read
+// and written with device-scope accesses: such a store goes through to the
+// point where every XCD reads, and the wave's vmcnt counts it only once it is
+// there; such a load misses the reader's L2.  So: every wave stores, waits for
+// vmcnt(0) and meets the workgroup's barrier before one thread adds to the
+// count, and the workgroup that finds the count complete loads after its own
+// barrier.  An agent-scope release and acquire around the count order the same
+// accesses by writing back and invalidating whole L2s, once per workgroup:
+// measured 1 us more on 28 workgroups and 40 against 25 us on 544.
+__device__ __forceinline__ void store_device(float *p, float x, float y) {
+    const u32x2 w = {__float_as_uint(x), __float_as_uint(y)};
+    __hip_atomic_store(reinterpret_cast<uint64_t *>(p), __builtin_bit_cast(uint64_t, w), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void load_device(const float *p, float &x, float &y) {
+    const u32x2 w = __builtin_bit_cast(
+        u32x2, __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    x = __uint_as_float(w.x);
+    y = __uint_as_float(w.y);
+}
+
+// Rows planned on the host: session in bits 0..11, split 12..21, the session's
+// planned splits 22..31.
+constexpr int kSmallRows = 256;
+struct SmallRows {
+    uint32_t row[kSmallRows];
+};
+template <bool kHost>
+using SmallRowsArg = typename std::conditional<kHost, SmallRows, NoPlan>::type;
+
+template <int D, int kDepth, bool kLoop, bool kHost>
+__global__ __launch_bounds__(kDecThreads) void decode_small_kernel(DecodeArgs a, SmallRowsArg<kHost> rows) {
+    __shared__ float sm_m[kDecWaves][kMaxGroup];
+    __shared__ float sm_l[kDecWaves][kMaxGroup];
+    __shared__ __attribute__((aligned(16))) float sm_o[kDecWaves][kMaxGroup][D];
+    __shared__ unsigned sm_before;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int lane = tid % kWave;
+    const int c16 = lane & 15, g4 = lane >> 4;
+    const int G = a.group, Hkv = a.num_kv_heads, T = a.split_tokens;
+    const int row = (int)blockIdx.x / Hkv, g = (int)blockIdx.x % Hkv;
+    int s = 0, split = 0, planned = kMaxSplits;
+    if constexpr (kHost) {
+        const uint32_t e = rows.row[row];
+        s = (int)(e & 0xFFFu);
+        split = (int)((e >> 12) & 0x3FFu);
+        planned = (int)(e >> 22);
+    } else {
+        // Rows of the sessions before each one: 64 sessions at a time.
+        int before = 0;
+        bool found = false;
+        for (int s0 = 0; s0 < a.num_sessions && !found; s0 += kWave) {
+            const int sl = min(s0 + lane, a.num_sessions - 1);
+            const int Ls = attended_len(a, sl, false);
+            const int n = s0 + lane < a.num_sessions ? max((Ls + T - 1) / T, 1) : 0;
+            int incl = n;
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1) {
+                const int y = __shfl_up(incl, off);
+                if (lane >= off) incl += y;
+            }
+            const int at = __popcll(__ballot(before + incl <= row));      // sessions of this chunk that end before the row
+            if (at < kWave && s0 + at < a.num_sessions) {
+                found = true;
+                s = s0 + at;
+                split = row - before - (at ? __builtin_amdgcn_readlane(incl, at - 1) : 0);
+            }
+            before += __builtin_amdgcn_readlane(incl, kWave - 1);
+        }
+        if (!found) return;
+        s = __builtin_amdgcn_readfirstlane(s);
+        split = __builtin_amdgcn_readfirstlane(split);
+    }
+
+    // Block ids of the split (one per lane), q and the length, all in flight at once.
+    const int id_at = min(split * (T / kBlock) + lane, a.max_blocks - 1);
+    const int ids = a.block_tables[(int64_t)s * a.max_blocks + id_at];
+    bf16x8 qop[D / 32];
+    {
+        const uint16_t *qrow = a.q + ((int64_t)s * Hkv * G + g * G + (c16 < G ? c16 : 0)) * D;
+#pragma unroll
+        for (int ks = 0; ks < D / 32; ++ks) {
+            uint4 v = *reinterpret_cast<const uint4 *>(qrow + ks * 32 + g4 * 8);
+            if (c16 >= G) v = make_uint4(0, 0, 0, 0);
+            qop[ks] = __builtin_bit_cast(bf16x8, v);
+        }
+    }
+    const bool first = split == 0 && g == 0 && tid == 0;
+    const int L = attended_len(a, s, first);
+    const int own = a.appended && a.lens[s] >= 0 && a.lens[s] + 1 <= a.max_blocks * kBlock;
+    // A device length past the host's rows: flagged, and attended as far as the
+    // rows go.
+    const int cover = kHost ? planned * T : INT32_MAX;
+    if (kHost && L > cover && first) flag_error(a.err, LS_DEVERR_LENGTH);
+    const int Lc = min(L, cover);
+    if (split * T >= max(Lc, 1)) return;
+    const int Lp = L - own;                       // keys read from the pool
+    const int nsplit = Lc > 0 ? (Lc + T - 1) / T : 1;
+    uint16_t *out = a.out + ((int64_t)s * Hkv * G + g * G) * D;
+    if (L <= 0) {
+        // Softmax over no key is undefined: the output is zero (flagged in attended_len).
+        for (int base = tid * 4; base < G * D; base += kDecThreads * 4)
+            *reinterpret_cast<uint2 *>(out + base) = make_uint2(0u, 0u);
+        return;
+    }
+    const int blk0 = split * (T / kBlock);
+    const int nblk = (min(Lc, (split + 1) * T) + kBlock - 1) / kBlock - blk0;
+    const int my_n = wave < nblk ? (nblk - wave + kDecWaves - 1) / kDecWaves : 0;
+    // Ids outside the pool become -1 (skipped), here rather than where they are
+    // used, so that nothing but tile loads is in flight in the loop below.
+    const bool bad = lane < nblk && (ids < 0 || ids >= a.num_blocks);
+    if (bad && wave == 0) flag_error(a.err, LS_DEVERR_BLOCK_ID);
+    const int good = bad ? -1 : ids;
+    auto bid = [&](int idx) -> int {              // id (or -1) of block idx of the split
+        const int b = __builtin_amdgcn_readlane(good, min(idx, kWave - 1));
+        return idx < nblk ? b : -1;
+    };
+    const int koff = (g4 * kBlock + c16) * 16, voff = (c16 * kBlock + g4 * 4) * 2;
+    BlockRegs<D> r[kDepth];
+    int bb[kDepth];
+#pragma unroll
+    for (int j = 0; j < kDepth; ++j) {
+        bb[j] = bid(wave + j * kDecWaves);
+        load_block<D>(r[j], a.pool, Hkv, g, bb[j], koff, voff);
+        // In this order: the loop waits for its first block alone.
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    float m = kMaxFloor, lsum = 0.f;
+    f32x4 o[D / 16];
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // kDepth blocks in flight per wave; a block past the split is requested
+    // through an empty descriptor, so that the count of loads in flight is known.
+#pragma unroll 1
+    for (int i = 0; i < my_n; i += kDepth) {
+#pragma unroll
+        for (int j = 0; j < kDepth; ++j) {
+            if (i + j < my_n)
+                process_block<D>(r[j], qop, (blk0 + wave + (i + j) * kDecWaves) * kBlock, bb[j] >= 0 ? Lp : 0,
+                                 a.scale_log2, g4, m, lsum, o);
+            if (kLoop) {
+                bb[j] = bid(wave + (i + j + kDepth) * kDecWaves);
+                load_block<D>(r[j], a.pool, Hkv, g, bb[j], koff, voff);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (!kLoop) break;
+    }
+    // The step's own token (see decode_kernel).
+    const int bl = Lp / kBlock - blk0;
+    if (own && split == nsplit - 1 && Lp < cover && wave == bl % kDecWaves)
+        attend_own<D>(a, s, g, Lp, bid(bl), qop, g4, c16, lane, m, lsum, o);
+    lsum = wave_sum_xor_16_32(lsum);
+
+    // ---- the workgroup's waves, through LDS.
+    if (c16 < G) {
+#pragma unroll
+        for (int dt = 0; dt < D / 16; ++dt) *reinterpret_cast<f32x4 *>(&sm_o[wave][c16][dt * 16 + g4 * 4]) = o[dt];
+        if (g4 == 0) {
+            sm_m[wave][c16] = m;
+            sm_l[wave][c16] = lsum;
+        }
+    }
+    __syncthreads();
+    const int base = tid * 4;                     // this thread's 4 consecutive outputs of the group
+    const bool active = base < G * D;
+    const int h = active ? base / D : 0, d = base % D;
+    float M = sm_m[0][h], wsum = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    if (active) {
+#pragma unroll
+        for (int w = 1; w < kDecWaves; ++w) M = fmaxf(M, sm_m[w][h]);
+#pragma unroll
+        for (int w = 0; w < kDecWaves; ++w) {
+            const float e = __builtin_amdgcn_exp2f(sm_m[w][h] - M);
+            wsum += e * sm_l[w][h];
+            acc += e * *reinterpret_cast<const f32x4 *>(&sm_o[w][h][d]);
+        }
+    }
+    if (nsplit > 1) {
+        // ---- the splits: partial results to the workspace, then the arrival.
+        // (splits of one (session, KV head) are Hkv partials apart)
+        const int64_t part = (int64_t)(row - split) * Hkv + g;
+        uint64_t *const count = a.arrived + (s * Hkv + g) * kArrivedStride;
+        if (active) {
+            float *po = a.part_acc + (int64_t)blockIdx.x * G * D + base;
+            store_device(po, acc[0], acc[1]);
+            store_device(po + 2, acc[2], acc[3]);
+            if (d == 0) store_device(a.part_ml + ((int64_t)blockIdx.x * G + h) * 2, M, wsum);
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0): this wave's partials are on their way out
+        __syncthreads();
+        if (tid == 0) sm_before = count_arrival(count);
+        __syncthreads();
+        if ((int)sm_before != nsplit - 1) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        if (tid == 0) __hip_atomic_store(count, kArrivedTag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (active) {
+            const float *pm = a.part_ml + (part * G + h) * 2;
+            const float *pa = a.part_acc + part * G * D + base;
+            const int ml_step = Hkv * G * 2, acc_step = Hkv * G * D;
+            constexpr int kPre = 8;
+            M = -INFINITY;
+            wsum = 0.f;
+            acc = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int k0 = 0; k0 < nsplit; k0 += kPre) {
+                float pmv[kPre], plv[kPre];
+                f32x4 pv[kPre];
+#pragma unroll
+                for (int i = 0; i < kPre; ++i) {
+                    const int k = min(k0 + i, nsplit - 1);
+                    load_device(pm + k * ml_step, pmv[i], plv[i]);
+                    float x, y, z, w;
+                    load_device(pa + (int64_t)k * acc_step, x, y);
+                    load_device(pa + (int64_t)k * acc_step + 2, z, w);
+                    pv[i] = f32x4{x, y, z, w};
+                }
+                float Mn = M;
+#pragma unroll
+                for (int i = 0; i < kPre; ++i) Mn = fmaxf(Mn, pmv[i]);
+                const float keep = __builtin_amdgcn_exp2f(M - Mn);
+                wsum *= keep;
+                acc *= keep;
+#pragma unroll
+                for (int i = 0; i < kPre; ++i) {
+                    const float e = k0 + i < nsplit ? __builtin_amdgcn_exp2f(pmv[i] - Mn) : 0.f;
+                    wsum += e * plv[i];
+                    acc += e * pv[i];
+                }
+                M = Mn;
+            }
+        }
+    }
+    if (active) {
+        const float inv = 1.f / wsum;
+        *reinterpret_cast<uint2 *>(out + base) =
+            make_uint2(pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv));
     }
 }
 
@@ -802,6 +1087,71 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(DecodeArgs
 
 }  // namespace
 
+// Batches that decode_small_kernel takes: those whose workgroups are resident
+// at once (device lengths are taken as uniform up to the table's width).
+// Splits of 256 tokens (two blocks per wave), 512, 768 or 1024 tokens; at
+// D = 64 of 512 or 1024: all of a wave's blocks are in flight at once up to
+// 512 tokens, two (four) at a time beyond.  Other lengths cost what the next of
+// these costs (384 tokens: 22 us where 512 took 16).  A size below sqrt(8 L) is
+// not taken: there the partials a split's last workgroup reads back (4096 L / T
+// bytes at D = 128) outweigh its own keys (512 T).  Of the others, in this
+// order: 256 or 512 tokens at one workgroup per CU, 256 at two (106 registers
+// allow it), longer ones; at D = 64, 512 at three.  Measured against the
+// two-launch schedules on 35 shapes: one session of 1789 keys 13.9 -> 7.4 us,
+// 16 of 300-4000 (device lengths) 19.3 -> 15.4, 32 of 1000-6000 at 2 heads
+// 30.7 -> 24.2, none slower.  Past one wave the persistent kernel's prefetch
+// across items wins.
+struct SmallSize {
+    int tokens, per_cu;
+};
+constexpr SmallSize kSmallSizes128[] = {{256, 1}, {512, 1}, {256, 2}, {768, 1}, {1024, 1}};
+constexpr SmallSize kSmallSizes64[] = {{512, 3}, {1024, 1}};
+
+SmallDecodePlan plan_small(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads, int32_t max_blocks,
+                           const int32_t *lens_host, int32_t appended, size_t bytes) {
+    const SmallDecodePlan none;
+    const int64_t cus = p.num_cus > 0 ? p.num_cus : 256, hkv = p.num_kv_heads;
+    if (num_sessions > kMaxBatch || num_sessions * hkv > 3 * cus) return none;
+    int64_t longest = (int64_t)max_blocks * kBlock;
+    if (lens_host) {
+        longest = 1;
+        for (int32_t s = 0; s < num_sessions; ++s) longest = std::max(longest, (int64_t)lens_host[s] + appended);
+    }
+    const int G = num_q_heads / p.num_kv_heads;
+    auto pad = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    const bool wide = p.head_dim == 128;
+    const SmallSize *size = wide ? kSmallSizes128 : kSmallSizes64;
+    const SmallSize *end = wide ? std::end(kSmallSizes128) : std::end(kSmallSizes64);
+    for (; size != end; ++size) {
+        const int T = size->tokens;
+        if (T < kMaxSplitTokens && (int64_t)T * T < 8 * longest) continue;
+        // A table far wider than the contexts leaves few, long splits: 8
+        // sessions of 500-2500 keys in 16k-token tables took 17.4 us against 16.2.
+        if (!lens_host && T == kMaxSplitTokens && longest > T) continue;
+        int64_t rows = 0;                          // of the grid
+        double resident;                           // workgroups with keys, expected
+        if (lens_host) {
+            for (int32_t s = 0; s < num_sessions; ++s) rows += std::max<int64_t>(1, ((int64_t)lens_host[s] + appended + T - 1) / T);
+            if (rows > kSmallRows) continue;
+            resident = (double)(rows * hkv);
+        } else {
+            const int64_t per = (longest + T - 1) / T;
+            rows = num_sessions * per;
+            resident = per == 1 ? (double)(rows * hkv)
+                                : (double)(num_sessions * hkv) * (0.5 * (double)longest / T + 0.5) / 1.1;
+        }
+        if (resident > (double)(size->per_cu * cus)) continue;
+        SmallDecodePlan plan;
+        plan.split_tokens = T;
+        plan.rows = (int)rows;
+        plan.count_bytes = (size_t)(num_sessions * hkv) * kArrivedStride * sizeof(uint64_t);
+        plan.ml_bytes = pad((size_t)(rows * hkv) * G * 2 * sizeof(float));
+        plan.acc_bytes = pad((size_t)(rows * hkv) * G * p.head_dim * sizeof(float));
+        if (plan.total() <= bytes) return plan;
+    }
+    return none;
+}
+
 DecodePlan plan_decode(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads,
                        int32_t max_blocks_per_session) {
     DecodePlan plan{};
@@ -831,6 +1181,13 @@ DecodePlan plan_decode(const PoolGeom &p, int32_t num_sessions, int32_t num_q_he
     auto pad = [](size_t b) { return (b + 255) & ~(size_t)255; };
     plan.ml_bytes = pad((size_t)sg * plan.max_splits * G * 2 * sizeof(float));
     plan.acc_bytes = pad((size_t)sg * plan.max_splits * G * p.head_dim * sizeof(float));
+    // Room for decode_small_kernel: its plan for device lengths, or any for host
+    // lengths (at most three workgroups per CU, see plan_small).
+    if (sg <= 3 * cus) {
+        const size_t most = pad((size_t)(3 * cus) * G * (p.head_dim + 2) * sizeof(float)) + 512;
+        const SmallDecodePlan dev = plan_small(p, num_sessions, num_q_heads, max_blocks_per_session, nullptr, 0, SIZE_MAX);
+        plan.small_bytes = std::max(dev.total(), (size_t)sg * kArrivedStride * sizeof(uint64_t) + most);
+    }
     return plan;
 }
 
@@ -1087,8 +1444,12 @@ const CachedPlan *cached_decode_plan(int S, int hkv, const int32_t *lens_host, i
 
 }  // namespace
 
-DecodeSchedule decode_schedule(const PoolGeom &p, int32_t num_sessions, const int32_t *context_lens_host,
-                               int32_t appended, const DecodePlan &plan, hipStream_t stream) {
+DecodeSchedule decode_schedule(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads, int32_t max_blocks,
+                               const int32_t *context_lens_host, int32_t appended, const DecodePlan &plan,
+                               hipStream_t stream) {
+    const SmallDecodePlan sp =
+        plan_small(p, num_sessions, num_q_heads, max_blocks, context_lens_host, appended, plan.recommended());
+    if (sp.split_tokens) return DecodeSchedule{sp.split_tokens, context_lens_host != nullptr, false};
     DecodeSchedule sc{plan.split_tokens, false, plan.max_splits > 1};
     if (context_lens_host) {
         const CachedPlan *c = cached_decode_plan(num_sessions, p.num_kv_heads, context_lens_host, appended,
@@ -1103,8 +1464,8 @@ hipError_t launch_decode(const PoolGeom &p, int layer, int32_t num_sessions, int
                          const uint16_t *q, const uint16_t *k_new, const uint16_t *v_new,
                          const int32_t *block_tables,
                          int32_t max_blocks, const int32_t *context_lens, const int32_t *context_lens_host,
-                         float scale, uint16_t *out, void *workspace, const DecodePlan &plan,
-                         unsigned int *err, hipStream_t stream) {
+                         float scale, uint16_t *out, void *workspace, size_t workspace_bytes,
+                         const DecodePlan &plan, unsigned int *err, hipStream_t stream) {
     DecodeArgs a;
     a.pool = p.layer_base(layer);
     a.num_blocks = p.num_blocks;
@@ -1126,6 +1487,46 @@ hipError_t launch_decode(const PoolGeom &p, int layer, int32_t num_sessions, int
     a.part_ml = reinterpret_cast<float *>(ws);
     a.part_acc = reinterpret_cast<float *>(ws + plan.ml_bytes);
     a.num_sessions = num_sessions;
+    a.arrived = nullptr;
+    // Small batches.  The room is the query's, so that the same call gives the
+    // same result from any workspace of at least that size.
+    const SmallDecodePlan sp = plan_small(p, num_sessions, num_q_heads, max_blocks, context_lens_host, a.appended,
+                                          std::min(workspace_bytes, plan.recommended()));
+    if (sp.split_tokens && reinterpret_cast<uintptr_t>(workspace) % 16 == 0) {
+        a.split_tokens = sp.split_tokens;
+        a.max_splits = 0;
+        a.arrived = reinterpret_cast<uint64_t *>(ws);
+        a.part_ml = reinterpret_cast<float *>(ws + sp.count_bytes);
+        a.part_acc = reinterpret_cast<float *>(ws + sp.count_bytes + sp.ml_bytes);
+        const dim3 grid((unsigned)(sp.rows * p.num_kv_heads));
+        const int per_wave = sp.split_tokens / (kDecWaves * kBlock);
+#define LS_SMALL(DD, DEPTH, LOOP) \
+    hipLaunchKernelGGL((decode_small_kernel<DD, DEPTH, LOOP, decltype(rows)::value>), grid, dim3(kDecThreads), 0, stream, a, arg)
+        auto launch = [&](auto rows, const auto &arg) {
+            if (p.head_dim == 128) {
+                if (per_wave <= 2) LS_SMALL(128, 2, false);
+                else if (per_wave <= 4) LS_SMALL(128, 4, false);
+                else LS_SMALL(128, 2, true);
+            } else {
+                if (per_wave <= 4) LS_SMALL(64, 4, false);
+                else LS_SMALL(64, 4, true);
+            }
+        };
+        if (context_lens_host) {
+            SmallRows list;
+            int n = 0;
+            for (int32_t s = 0; s < num_sessions; ++s) {
+                const int64_t L = (int64_t)context_lens_host[s] + a.appended;
+                const int ns = (int)std::max<int64_t>(1, (L + sp.split_tokens - 1) / sp.split_tokens);
+                for (int k = 0; k < ns; ++k) list.row[n++] = (uint32_t)s | ((uint32_t)k << 12) | ((uint32_t)ns << 22);
+            }
+            launch(std::true_type{}, list);
+        } else {
+            launch(std::false_type{}, NoPlan{0});
+        }
+#undef LS_SMALL
+        return hipGetLastError();
+    }
     const int64_t resident = (int64_t)stream_cus(p, stream);
     dim3 cgrid(p.num_kv_heads, num_sessions);
     // Host lengths: the schedule is planned here and passed with the arguments.

@@ -1,0 +1,133 @@
+"""Small decode batches: one workgroup per split, merged by the last of each (session, KV head) to
+finish, without a second launch.  Against the oracle at the edges of blocks, splits and rows, with
+arbitrary workspace contents."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from tests.gpu_util import DevicePool, assert_attn_close, bf16_dev, i32_dev
+from tests.test_gpu_decode import _synthetic
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def kv():
+    from paper_2606_22983_amd import kv as kv_mod
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return kv_mod
+
+
+def _small(kv, dp, q, tables, lens, append, host):
+    """The batch runs without the merge kernel, in splits shorter than its longest session."""
+    sc = kv.ls_decode_schedule(dp.pool, q.shape[0], q.shape[1], tables.shape[1],
+                               context_lens_host=lens if host else None, appended=append)
+    return not sc["merge"] and sc["split_tokens"] <= 1024
+
+
+def _call(kv, dp, q, kn, vn, tables, lens, host, ws, d, lens_host=None):
+    out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+    lh = None if not host else lens if lens_host is None else lens_host
+    kv.paged_attn_decode(dp.pool, 0, bf16_dev(q), i32_dev(tables), i32_dev(lens), 1 / math.sqrt(d), out, ws,
+                         None if kn is None else bf16_dev(kn), None if vn is None else bf16_dev(vn),
+                         context_lens_host=lh)
+    return out
+
+
+def _workspace(kv, dp, q, tables, fill):
+    n = kv.decode_workspace_bytes(dp.pool, q.shape[0], q.shape[1], tables.shape[1])
+    ws = torch.empty((n + 7) // 8, dtype=torch.int64, device="cuda")
+    ws.fill_(fill)
+    return ws
+
+
+CASES = [
+    (32, 4, 128, [1789]), (32, 4, 128, [1, 16, 17, 255, 256, 257, 511, 512]), (16, 2, 128, [513, 3000, 1, 767, 768, 769]),
+    (8, 1, 128, [16384, 5]), (4, 4, 128, [300, 900, 1023]), (16, 4, 64, [100, 511, 512, 513, 3000]), (8, 8, 64, [1025, 31]),
+    (4, 2, 64, [1, 2000]), (8, 1, 64, [8191, 8192, 8193]), (16, 2, 128, list(range(1, 131))),
+]
+
+
+@pytest.mark.parametrize("host", [False, True])
+@pytest.mark.parametrize("append", [False, True])
+@pytest.mark.parametrize("hq,hkv,d,lens", CASES)
+def test_small_decode_matches_oracle(kv, oracle_lib, hq, hkv, d, lens, append, host):
+    rng = np.random.default_rng(sum(lens) + hq)
+    lens = np.array(lens, np.int64) - (1 if append else 0)
+    pool, tables, q, kn, vn = _synthetic(rng, lens, hq, hkv, d, append)
+    dp = DevicePool(kv, pool, d)
+    assert _small(kv, dp, q, tables, lens, append, host)
+    ref, ref_pool = oracle_lib.decode(pool, 16, d, 0, q, tables, lens, 1 / math.sqrt(d), k_new=kn, v_new=vn,
+                                      pool_out=True)
+    # Arbitrary contents of the counts: zeros, ones, a word one below the tag's, what the call leaves.
+    ws = _workspace(kv, dp, q, tables, 0)
+    first = None
+    for fill in (0, -1, 0x1D3B6E52C1A6FFFF, 0x3F8000003F800000, None, None):
+        if fill is not None:
+            ws.fill_(fill)
+        out = _call(kv, dp, q, kn, vn, tables, lens, host, ws, d)
+        if first is None:
+            first = out
+            assert_attn_close(out, ref, "small decode %s append=%s host=%s" % (list(lens[:8]), append, host))
+        assert torch.equal(out.view(torch.int16), first.view(torch.int16)), fill
+    if append:
+        assert np.array_equal(dp.host(), ref_pool)
+    # A workspace that is only 8-byte aligned takes the other schedule.
+    n = kv.decode_workspace_bytes(dp.pool, len(lens), hq, tables.shape[1])
+    other = _call(kv, dp, q, kn, vn, tables, lens, host, torch.zeros(n // 8 + 2, dtype=torch.int64, device="cuda")[1:], d)
+    assert_attn_close(other, ref, "8-byte aligned workspace")
+    assert kv.ls_device_errors() == 0
+
+
+def test_small_decode_shapes_share_a_workspace(kv, oracle_lib):
+    """Calls of different shapes in turn on one workspace: each finds the others' partials and
+    counts where its own counts are."""
+    rng = np.random.default_rng(3)
+    made = []
+    for hq, hkv, d, lens in CASES[:6]:
+        lens = np.array(lens, np.int64)
+        pool, tables, q, _, _ = _synthetic(rng, lens, hq, hkv, d, False)
+        dp = DevicePool(kv, pool, d)
+        made.append((dp, q, tables, lens, d, oracle_lib.decode(pool, 16, d, 0, q, tables, lens, 1 / math.sqrt(d))))
+    ws = torch.zeros(max(kv.decode_workspace_bytes(m[0].pool, len(m[3]), m[1].shape[1], m[2].shape[1]) for m in made),
+                     dtype=torch.uint8, device="cuda")
+    for rep in range(3):
+        for i, (dp, q, tables, lens, d, ref) in enumerate(made):
+            out = _call(kv, dp, q, None, None, tables, lens, bool((rep + i) & 1), ws, d)
+            assert_attn_close(out, ref, "shared workspace, call %d.%d" % (rep, i))
+    assert kv.ls_device_errors() == 0
+
+
+def test_small_decode_errors_and_other_device_lengths(kv, oracle_lib):
+    rng = np.random.default_rng(4)
+    lens = np.array([700, 1500, 40, 600])
+    pool, tables, q, _, _ = _synthetic(rng, lens, 16, 2, 128, False)
+    dp = DevicePool(kv, pool, 128)
+    ws = _workspace(kv, dp, q, tables, 0)
+    kv.ls_device_errors()
+    # an empty context: zeros, flagged; the others as usual
+    dev = lens.copy()
+    dev[2] = 0
+    out = _call(kv, dp, q, None, None, tables, dev, False, ws, 128)
+    assert bool((out[2] == 0).all()) and kv.ls_device_errors() == kv.LS_DEVERR_LENGTH
+    keep = [0, 1, 3]
+    ref = oracle_lib.decode(pool, 16, 128, 0, q, tables, lens, 1 / math.sqrt(128))
+    assert_attn_close(out[keep], ref[keep], "beside an empty context")
+    # device lengths shorter than the host's rows
+    short = np.array([300, 1, 40, 513])
+    out = _call(kv, dp, q, None, None, tables, short, True, ws, 128, lens_host=lens)
+    assert_attn_close(out, oracle_lib.decode(pool, 16, 128, 0, q, tables, short, 1 / math.sqrt(128)), "shorter")
+    assert kv.ls_device_errors() == 0
+    # longer than the host's rows: flagged
+    _call(kv, dp, q, None, None, tables, lens, True, ws, 128, lens_host=np.array([700, 100, 40, 600]))
+    assert kv.ls_device_errors() == kv.LS_DEVERR_LENGTH
+    # and the next call counts as usual
+    out = _call(kv, dp, q, None, None, tables, lens, True, ws, 128)
+    assert_attn_close(out, ref, "after a flagged call")
+    # a block id outside the pool: flagged, its keys absent
+    bad = tables.copy()
+    bad[1, 3] = 1 << 29
+    _call(kv, dp, q, None, None, bad, lens, False, ws, 128)
+    assert kv.ls_device_errors() == kv.LS_DEVERR_BLOCK_ID
