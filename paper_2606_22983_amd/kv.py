@@ -82,7 +82,7 @@ def _check(status: int, where: str):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _shape(t: torch.Tensor, name: str, shape, dtype=None):
@@ -109,13 +109,21 @@ def _nbytes(t: torch.Tensor) -> int:
     return t.numel() * t.element_size()
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream):
+    """The HIP stream's handle (None: torch's current stream of the current device)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 _BF16 = (torch.bfloat16, torch.int16)
+_I32 = (torch.int32,)
+
+
+def _fits(t: torch.Tensor, shape, dtypes) -> bool:
+    """Whether t passes _shape and _dev, in one test.  A small batch's decode takes 7 us of GPU
+    time, and a call's checks, one by one, took more than that (15 us a call on the host)."""
+    return t.shape == shape and t.dtype in dtypes and t.is_cuda and t.is_contiguous()
 
 
 def version() -> str:
@@ -181,10 +189,33 @@ def _host_i32(a, name: str, n: int):
     """Host int32 copy (kept alive by the caller) of an optional length array."""
     if a is None:
         return None, None
-    arr = np.ascontiguousarray(np.asarray(a).reshape(-1), dtype=np.int32)
+    if type(a) is np.ndarray and a.dtype == np.int32 and a.flags.c_contiguous:
+        arr = a
+    else:
+        arr = np.ascontiguousarray(np.asarray(a).reshape(-1), dtype=np.int32)
     if arr.size != n:
         raise ValueError("%s must hold %d values (got %d)" % (name, n, arr.size))
-    return arr, ctypes.c_void_p(arr.ctypes.data)
+    return arr, arr.__array_interface__["data"][0]
+
+
+def _decode_args(s, hq, hkv, d, q, out, block_tables, context_lens, k_new, v_new):
+    """Shapes, types and devices of a decode call's tensors (raises ValueError)."""
+    rows, new = (s, hq, d), (s, hkv, d)
+    if (_fits(q, rows, _BF16) and _fits(out, rows, _BF16) and _fits(context_lens, (s,), _I32)
+            and block_tables.dim() == 2 and _fits(block_tables, (s, block_tables.shape[1]), _I32)
+            and (k_new is None or _fits(k_new, new, _BF16)) and (v_new is None or _fits(v_new, new, _BF16))):
+        return
+    _shape(q, "q", rows, _BF16)
+    _shape(out, "out", rows, _BF16)
+    _shape(block_tables, "block_tables", (s, None), torch.int32)
+    _shape(context_lens, "context_lens", (s,), torch.int32)
+    for t, name in ((k_new, "k_new"), (v_new, "v_new")):
+        if t is not None:
+            _shape(t, name, new, _BF16)
+    for t, name in ((q, "q"), (out, "out"), (block_tables, "block_tables"), (context_lens, "context_lens"),
+                    (k_new, "k_new"), (v_new, "v_new")):
+        if t is not None:
+            _dev(t, name)
 
 
 def paged_attn_decode(pool: KVPool, layer: int, q: torch.Tensor, block_tables: torch.Tensor,
@@ -198,18 +229,9 @@ def paged_attn_decode(pool: KVPool, layer: int, q: torch.Tensor, block_tables: t
         raise ValueError("q must be [S][Hq][D]")
     s, hq = q.shape[0], q.shape[1]
     d, hkv = pool.head_dim, pool.num_kv_heads
-    _shape(q, "q", (s, hq, d), _BF16)
-    _shape(out, "out", (s, hq, d), _BF16)
-    _shape(block_tables, "block_tables", (s, None), torch.int32)
-    _shape(context_lens, "context_lens", (s,), torch.int32)
-    for t, name in ((k_new, "k_new"), (v_new, "v_new")):
-        if t is not None:
-            _shape(t, name, (s, hkv, d), _BF16)
-    for t, name in ((q, "q"), (out, "out"), (block_tables, "block_tables"),
-                    (context_lens, "context_lens"), (workspace, "workspace"), (k_new, "k_new"),
-                    (v_new, "v_new")):
-        if t is not None:
-            _dev(t, name)
+    _decode_args(s, hq, hkv, d, q, out, block_tables, context_lens, k_new, v_new)
+    if not (workspace.is_cuda and workspace.is_contiguous()):
+        _dev(workspace, "workspace")
     keep, hl = _host_i32(context_lens_host, "context_lens_host", s)
     _check(_lib.paged_attn_decode(pool.handle, layer, s, hq, _ptr(q), _ptr(k_new), _ptr(v_new),
                                   _ptr(block_tables), block_tables.shape[1], _ptr(context_lens), hl,
@@ -241,17 +263,7 @@ def paged_attn_decode_static(pool: KVPool, layer: int, q: torch.Tensor, block_ta
         raise ValueError("q must be [S][Hq][D]")
     s, hq = q.shape[0], q.shape[1]
     d, hkv = pool.head_dim, pool.num_kv_heads
-    _shape(q, "q", (s, hq, d), _BF16)
-    _shape(out, "out", (s, hq, d), _BF16)
-    _shape(block_tables, "block_tables", (s, None), torch.int32)
-    _shape(context_lens, "context_lens", (s,), torch.int32)
-    for t, name in ((k_new, "k_new"), (v_new, "v_new")):
-        if t is not None:
-            _shape(t, name, (s, hkv, d), _BF16)
-    for t, name in ((q, "q"), (out, "out"), (block_tables, "block_tables"),
-                    (context_lens, "context_lens"), (k_new, "k_new"), (v_new, "v_new")):
-        if t is not None:
-            _dev(t, name)
+    _decode_args(s, hq, hkv, d, q, out, block_tables, context_lens, k_new, v_new)
     keep, hl = _host_i32(context_lens_host, "context_lens_host", s)
     _check(_lib.paged_attn_decode_static(pool.handle, layer, s, hq, _ptr(q), _ptr(k_new), _ptr(v_new),
                                          _ptr(block_tables), block_tables.shape[1], _ptr(context_lens),
@@ -277,19 +289,24 @@ def paged_attn_prefill(pool: KVPool, layer: int, q: torch.Tensor, cu_new_lens: t
     total, hq = q.shape[0], q.shape[1]
     s = reused_lens.shape[0] if reused_lens.dim() == 1 else -1
     d, hkv = pool.head_dim, pool.num_kv_heads
-    _shape(q, "q", (total, hq, d), _BF16)
-    _shape(out, "out", (total, hq, d), _BF16)
-    _shape(reused_lens, "reused_lens", (None,), torch.int32)
-    _shape(cu_new_lens, "cu_new_lens", (s + 1,), torch.int32)
-    _shape(block_tables, "block_tables", (s, None), torch.int32)
-    for t, name in ((k_new, "k_new"), (v_new, "v_new")):
-        if t is not None:
-            _shape(t, name, (total, hkv, d), _BF16)
-    for t, name in ((q, "q"), (out, "out"), (cu_new_lens, "cu_new_lens"),
-                    (reused_lens, "reused_lens"), (block_tables, "block_tables"), (k_new, "k_new"),
-                    (v_new, "v_new")):
-        if t is not None:
-            _dev(t, name)
+    rows, new = (total, hq, d), (total, hkv, d)
+    if not (_fits(q, rows, _BF16) and _fits(out, rows, _BF16) and _fits(reused_lens, (s,), _I32)
+            and _fits(cu_new_lens, (s + 1,), _I32) and block_tables.dim() == 2
+            and _fits(block_tables, (s, block_tables.shape[1]), _I32)
+            and (k_new is None or _fits(k_new, new, _BF16)) and (v_new is None or _fits(v_new, new, _BF16))):
+        _shape(q, "q", (total, hq, d), _BF16)
+        _shape(out, "out", (total, hq, d), _BF16)
+        _shape(reused_lens, "reused_lens", (None,), torch.int32)
+        _shape(cu_new_lens, "cu_new_lens", (s + 1,), torch.int32)
+        _shape(block_tables, "block_tables", (s, None), torch.int32)
+        for t, name in ((k_new, "k_new"), (v_new, "v_new")):
+            if t is not None:
+                _shape(t, name, (total, hkv, d), _BF16)
+        for t, name in ((q, "q"), (out, "out"), (cu_new_lens, "cu_new_lens"),
+                        (reused_lens, "reused_lens"), (block_tables, "block_tables"), (k_new, "k_new"),
+                        (v_new, "v_new")):
+            if t is not None:
+                _dev(t, name)
     keep, hl = _host_i32(lens_host, "lens_host", 2 * s)
     if workspace is not None:
         _dev(workspace, "workspace")
@@ -308,7 +325,7 @@ def _host_ids(ids):
     if ids is None:
         return None, None
     arr = np.ascontiguousarray(ids, dtype=np.int32)
-    return arr, ctypes.c_void_p(arr.ctypes.data)
+    return arr, arr.__array_interface__["data"][0]
 
 
 def _copy_args(pool: KVPool, block_ids: torch.Tensor, staging: torch.Tensor, ring, max_gbps):
