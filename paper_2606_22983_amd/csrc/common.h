@@ -48,6 +48,7 @@ unsigned int *device_error_word();
 // (session, KV head).  split_tokens 0: the batch is not small.
 struct SmallDecodePlan {
     int split_tokens = 0;
+    bool single = false;            // no session is split: a row per session
     int rows = 0;                   // (session, split) rows (device lengths: their bound)
     size_t count_bytes = 0;         // uint64 [S][Hkv] arrival counts, 128 bytes apart
     size_t ml_bytes = 0;            // fp32 [rows][Hkv][G][2]

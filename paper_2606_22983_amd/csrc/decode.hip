@@ -797,12 +797,15 @@ __global__ __launch_bounds__(kDecThreads) void decode_small_kernel(DecodeArgs a,
     const int c16 = lane & 15, g4 = lane >> 4;
     const int G = a.group, Hkv = a.num_kv_heads, T = a.split_tokens;
     const int row = (int)blockIdx.x / Hkv, g = (int)blockIdx.x % Hkv;
-    int s = 0, split = 0, planned = kMaxSplits;
+    int s = 0, split = 0, planned = INT32_MAX / kMaxSplitTokens;
     if constexpr (kHost) {
         const uint32_t e = rows.row[row];
         s = (int)(e & 0xFFFu);
         split = (int)((e >> 12) & 0x3FFu);
         planned = (int)(e >> 22);
+    } else if (a.max_splits == 1) {
+        s = row;                               // no session is split
+        planned = 1;
     } else {
         // Rows of the sessions before each one: 64 sessions at a time.
         int before = 0;
@@ -848,8 +851,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_small_kernel(DecodeArgs a,
     const int own = a.appended && a.lens[s] >= 0 && a.lens[s] + 1 <= a.max_blocks * kBlock;
     // A device length past the host's rows: flagged, and attended as far as the
     // rows go.
-    const int cover = kHost ? planned * T : INT32_MAX;
-    if (kHost && L > cover && first) flag_error(a.err, LS_DEVERR_LENGTH);
+    const int cover = planned * T;
+    if (L > cover && first) flag_error(a.err, LS_DEVERR_LENGTH);
     const int Lc = min(L, cover);
     if (split * T >= max(Lc, 1)) return;
     const int Lp = L - own;                       // keys read from the pool
@@ -1100,7 +1103,10 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(DecodeArgs
 // two-launch schedules on 35 shapes: one session of 1789 keys 13.9 -> 7.4 us,
 // 16 of 300-4000 (device lengths) 19.3 -> 15.4, 32 of 1000-6000 at 2 heads
 // 30.7 -> 24.2, none slower.  Past one wave the persistent kernel's prefetch
-// across items wins.
+// across items wins, unless no session is longer than a split: then each
+// (session, KV head) has one workgroup, and any number of them is taken (200
+// sessions of 50-300 keys at 4 heads 37.6 -> 25.3 us, 64 of 300-900 with device
+// lengths 30.2 -> 20.8).
 struct SmallSize {
     int tokens, per_cu;
 };
@@ -1111,7 +1117,7 @@ SmallDecodePlan plan_small(const PoolGeom &p, int32_t num_sessions, int32_t num_
                            const int32_t *lens_host, int32_t appended, size_t bytes) {
     const SmallDecodePlan none;
     const int64_t cus = p.num_cus > 0 ? p.num_cus : 256, hkv = p.num_kv_heads;
-    if (num_sessions > kMaxBatch || num_sessions * hkv > 3 * cus) return none;
+    if (num_sessions > kMaxBatch) return none;
     int64_t longest = (int64_t)max_blocks * kBlock;
     if (lens_host) {
         longest = 1;
@@ -1125,9 +1131,20 @@ SmallDecodePlan plan_small(const PoolGeom &p, int32_t num_sessions, int32_t num_
     for (; size != end; ++size) {
         const int T = size->tokens;
         if (T < kMaxSplitTokens && (int64_t)T * T < 8 * longest) continue;
+        SmallDecodePlan plan;
+        if (T >= longest) {
+            // No session is split: no partials and no counts, whatever the batch
+            // (but the host plan's prefetch wins on many 1024-token items at
+            // D = 64: 500 sessions of 300-1000 keys at 2 heads, 37.5 against 38.1 us).
+            if (!wide && T == kMaxSplitTokens && lens_host && num_sessions * hkv > 2 * cus) return none;
+            plan.split_tokens = T;
+            plan.rows = num_sessions;
+            plan.single = true;
+            return plan;
+        }
         // A table far wider than the contexts leaves few, long splits: 8
         // sessions of 500-2500 keys in 16k-token tables took 17.4 us against 16.2.
-        if (!lens_host && T == kMaxSplitTokens && longest > T) continue;
+        if (!lens_host && T == kMaxSplitTokens) continue;
         int64_t rows = 0;                          // of the grid
         double resident;                           // workgroups with keys, expected
         if (lens_host) {
@@ -1135,13 +1152,10 @@ SmallDecodePlan plan_small(const PoolGeom &p, int32_t num_sessions, int32_t num_
             if (rows > kSmallRows) continue;
             resident = (double)(rows * hkv);
         } else {
-            const int64_t per = (longest + T - 1) / T;
-            rows = num_sessions * per;
-            resident = per == 1 ? (double)(rows * hkv)
-                                : (double)(num_sessions * hkv) * (0.5 * (double)longest / T + 0.5) / 1.1;
+            rows = num_sessions * ((longest + T - 1) / T);
+            resident = (double)(num_sessions * hkv) * (0.5 * (double)longest / T + 0.5) / 1.1;
         }
         if (resident > (double)(size->per_cu * cus)) continue;
-        SmallDecodePlan plan;
         plan.split_tokens = T;
         plan.rows = (int)rows;
         plan.count_bytes = (size_t)(num_sessions * hkv) * kArrivedStride * sizeof(uint64_t);
@@ -1492,9 +1506,9 @@ hipError_t launch_decode(const PoolGeom &p, int layer, int32_t num_sessions, int
     // same result from any workspace of at least that size.
     const SmallDecodePlan sp = plan_small(p, num_sessions, num_q_heads, max_blocks, context_lens_host, a.appended,
                                           std::min(workspace_bytes, plan.recommended()));
-    if (sp.split_tokens && reinterpret_cast<uintptr_t>(workspace) % 16 == 0) {
+    if (sp.split_tokens && (sp.single || reinterpret_cast<uintptr_t>(workspace) % 16 == 0)) {
         a.split_tokens = sp.split_tokens;
-        a.max_splits = 0;
+        a.max_splits = sp.single ? 1 : 0;
         a.arrived = reinterpret_cast<uint64_t *>(ws);
         a.part_ml = reinterpret_cast<float *>(ws + sp.count_bytes);
         a.part_acc = reinterpret_cast<float *>(ws + sp.count_bytes + sp.ml_bytes);
@@ -1512,7 +1526,7 @@ hipError_t launch_decode(const PoolGeom &p, int layer, int32_t num_sessions, int
                 else LS_SMALL(64, 4, true);
             }
         };
-        if (context_lens_host) {
+        if (context_lens_host && !sp.single) {
             SmallRows list;
             int n = 0;
             for (int32_t s = 0; s < num_sessions; ++s) {

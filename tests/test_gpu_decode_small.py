@@ -47,6 +47,8 @@ CASES = [
     (32, 4, 128, [1789]), (32, 4, 128, [1, 16, 17, 255, 256, 257, 511, 512]), (16, 2, 128, [513, 3000, 1, 767, 768, 769]),
     (8, 1, 128, [16384, 5]), (4, 4, 128, [300, 900, 1023]), (16, 4, 64, [100, 511, 512, 513, 3000]), (8, 8, 64, [1025, 31]),
     (4, 2, 64, [1, 2000]), (8, 1, 64, [8191, 8192, 8193]), (16, 2, 128, list(range(1, 131))),
+    # no session is split: any number of workgroups
+    (32, 4, 128, list(range(1, 301))), (8, 8, 64, list(range(120, 240))), (8, 2, 128, [1024, 1023, 513] * 60),
 ]
 
 
@@ -122,6 +124,8 @@ def test_small_decode_errors_and_other_device_lengths(kv, oracle_lib):
     assert kv.ls_device_errors() == 0
     # longer than the host's rows: flagged
     _call(kv, dp, q, None, None, tables, lens, True, ws, 128, lens_host=np.array([700, 100, 40, 600]))
+    assert kv.ls_device_errors() == kv.LS_DEVERR_LENGTH
+    _call(kv, dp, q, None, None, tables, lens, True, ws, 128, lens_host=np.array([200, 100, 40, 250]))
     assert kv.ls_device_errors() == kv.LS_DEVERR_LENGTH
     # and the next call counts as usual
     out = _call(kv, dp, q, None, None, tables, lens, True, ws, 128)
