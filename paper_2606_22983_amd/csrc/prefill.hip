@@ -254,8 +254,10 @@ __device__ __forceinline__ void order_phase() {
 
 // kHost: the schedule comes with the arguments; kSplit: some of its items are
 // parts of a query tile's keys.  (The calls that split nothing keep a kernel
-// without that code: it costs the D = 128 loop two spilled registers.)
-template <int D, bool kHost, bool kSplit = false>
+// without that code: the D = 128 loop has no register to spare, and the code
+// cost the 32-turn batch 0.9%.)
+// kSkip: waves skip the key tiles none of their rows sees.
+template <int D, bool kHost, bool kSplit, bool kSkip>
 __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, PrefillPlanArg<kHost, kSplit> plan) {
     using C = Geo<D>;
     constexpr int KS = D / 32;           // 32-dim k-steps of QK
@@ -345,6 +347,15 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
         __builtin_amdgcn_s_waitcnt(0x0F70);
         // smallest causal limit among this wave's rows: units past it need masking
         const int wave_lim_min = c + min(j0 + (wave * kWaveRows) / G, n - 1) - key_base;
+
+        // Key tiles some row of this wave sees: none when its rows are all padding,
+        // fewer than the workgroup's where the tile spans many tokens.  Past them
+        // the wave only loads and meets the barriers, and the wave it shares its
+        // SIMD with runs alone (32 turns of 8 tokens over 2050, 8 KV heads: 82.4 ->
+        // 64.9 us).  Large turns have no such waves, and the other bound costs
+        // their loop 0.5%.
+        const int jw_first = j0 + wave * kWaveRows / G, jw_last = min(j0 + (wave * kWaveRows + kWaveRows - 1) / G, n - 1);
+        const int wave_tiles = !kSkip ? ntiles : jw_first < n ? min(ntiles, (max(c + jw_last - key_base + 1, 0) + kKeyTile - 1) / kKeyTile) : 0;
 
         // ---- this wave's share of every stage: kLoadsK kilobytes of one K block
         // and of one V block (block 'blk' of the stage), at fixed lane offsets.
@@ -631,8 +642,8 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
             const int32_t ik = idk, iv = idv;
             idk = id_k(j + 3);
             idv = id_v(j + 3);
-            const bool live = j < ntiles;
-            if (live && (j + 1) * kKeyTile > kv_len) zero_v_tail(vs, j);
+            const bool live = j < wave_tiles;
+            if (j < ntiles && (j + 1) * kKeyTile > kv_len) zero_v_tail(vs, j);
             load_k(kn, ik);
             load_v(vn, iv);
             if (live) {
@@ -665,7 +676,7 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
                 order_phase<0, kPhaseMfma, 2 * KS, 0, kScaleValu>();
                 __builtin_amdgcn_s_setprio(0);
                 settle(sb2, sa, pop_o, us_o);
-                if (j == ntiles - 1) {                  // the last unit's P V
+                if (j == wave_tiles - 1) {              // the last unit's P V
                     read_v(vs, 1);
                     pv_mfma(pop_o);
                 }
@@ -1227,6 +1238,9 @@ hipError_t launch_prefill(const PoolGeom &p, int layer, int32_t num_sessions, in
     a.max_blocks = max_blocks;
     a.scale_log2 = scale * kLog2eP;
     a.err = err;
+    // Half a tile of padding per turn, on average: from an eighth of the rows on,
+    // waves without rows or keys skip their work.
+    const bool skip = 4LL * num_sessions * (kPreRows / a.group) >= total_tokens;
     a.resident = 0;
     a.queue = nullptr;
     a.part_ml = nullptr;
@@ -1263,9 +1277,9 @@ hipError_t launch_prefill(const PoolGeom &p, int layer, int32_t num_sessions, in
             a.part_o = reinterpret_cast<float *>(parts + (size_t)kPrefillSplitPieces * kPreRows * 2 * sizeof(float));
             const dim3 grid = queue_grid(items), mgrid((unsigned)(split_tiles * (kPreWaves * kRT * p.head_dim / 16 / kMergeWaves)));
             if (p.head_dim == 128)
-                hipLaunchKernelGGL((prefill_kernel<128, true, true>), grid, dim3(kPreThreads), 0, stream, a, plan);
+                hipLaunchKernelGGL((prefill_kernel<128, true, true, true>), grid, dim3(kPreThreads), 0, stream, a, plan);
             else
-                hipLaunchKernelGGL((prefill_kernel<64, true, true>), grid, dim3(kPreThreads), 0, stream, a, plan);
+                hipLaunchKernelGGL((prefill_kernel<64, true, true, true>), grid, dim3(kPreThreads), 0, stream, a, plan);
             if (hipError_t e = hipGetLastError()) return e;
             if (p.head_dim == 128)
                 hipLaunchKernelGGL(prefill_merge_kernel<128>, mgrid, dim3(kMergeThreads), 0, stream, a, merge);
@@ -1284,10 +1298,14 @@ hipError_t launch_prefill(const PoolGeom &p, int layer, int32_t num_sessions, in
             grid = queue_grid(total);
         }
         const PrefillHostPlan &whole = plan;
-        if (p.head_dim == 128)
-            hipLaunchKernelGGL((prefill_kernel<128, true>), grid, dim3(kPreThreads), 0, stream, a, whole);
+        if (p.head_dim == 128 && skip)
+            hipLaunchKernelGGL((prefill_kernel<128, true, false, true>), grid, dim3(kPreThreads), 0, stream, a, whole);
+        else if (p.head_dim == 128)
+            hipLaunchKernelGGL((prefill_kernel<128, true, false, false>), grid, dim3(kPreThreads), 0, stream, a, whole);
+        else if (skip)
+            hipLaunchKernelGGL((prefill_kernel<64, true, false, true>), grid, dim3(kPreThreads), 0, stream, a, whole);
         else
-            hipLaunchKernelGGL((prefill_kernel<64, true>), grid, dim3(kPreThreads), 0, stream, a, whole);
+            hipLaunchKernelGGL((prefill_kernel<64, true, false, false>), grid, dim3(kPreThreads), 0, stream, a, whole);
         return hipGetLastError();
     }
     // An XCD holds at most ceil(pairs / 8) pairs of at most qtiles items each;
@@ -1298,10 +1316,14 @@ hipError_t launch_prefill(const PoolGeom &p, int layer, int32_t num_sessions, in
     a.resident = grid <= stream_cus(p, stream) ? 1 : 0;
     const PrefillNoPlan none{0};
     const dim3 g((unsigned)grid);
-    if (p.head_dim == 128)
-        hipLaunchKernelGGL((prefill_kernel<128, false>), g, dim3(kPreThreads), 0, stream, a, none);
+    if (p.head_dim == 128 && skip)
+        hipLaunchKernelGGL((prefill_kernel<128, false, false, true>), g, dim3(kPreThreads), 0, stream, a, none);
+    else if (p.head_dim == 128)
+        hipLaunchKernelGGL((prefill_kernel<128, false, false, false>), g, dim3(kPreThreads), 0, stream, a, none);
+    else if (skip)
+        hipLaunchKernelGGL((prefill_kernel<64, false, false, true>), g, dim3(kPreThreads), 0, stream, a, none);
     else
-        hipLaunchKernelGGL((prefill_kernel<64, false>), g, dim3(kPreThreads), 0, stream, a, none);
+        hipLaunchKernelGGL((prefill_kernel<64, false, false, false>), g, dim3(kPreThreads), 0, stream, a, none);
     return hipGetLastError();
 }
 
