@@ -1196,9 +1196,11 @@ DecodePlan plan_decode(const PoolGeom &p, int32_t num_sessions, int32_t num_q_he
     plan.ml_bytes = pad((size_t)sg * plan.max_splits * G * 2 * sizeof(float));
     plan.acc_bytes = pad((size_t)sg * plan.max_splits * G * p.head_dim * sizeof(float));
     // Room for decode_small_kernel: its plan for device lengths, or any for host
-    // lengths (at most three workgroups per CU, see plan_small).
+    // lengths (at most three workgroups per CU, see plan_small, and one per split).
     if (sg <= 3 * cus) {
-        const size_t most = pad((size_t)(3 * cus) * G * (p.head_dim + 2) * sizeof(float)) + 512;
+        const int64_t shortest = p.head_dim == 128 ? kSmallSizes128[0].tokens : kSmallSizes64[0].tokens;
+        const int64_t wgs = std::min(3 * cus, sg * ((max_tokens + shortest - 1) / shortest));
+        const size_t most = pad((size_t)wgs * G * (p.head_dim + 2) * sizeof(float)) + 512;
         const SmallDecodePlan dev = plan_small(p, num_sessions, num_q_heads, max_blocks_per_session, nullptr, 0, SIZE_MAX);
         plan.small_bytes = std::max(dev.total(), (size_t)sg * kArrivedStride * sizeof(uint64_t) + most);
     }

@@ -38,7 +38,8 @@ def _call(kv, dp, q, kn, vn, n, c, tables, d, ws_bytes, lens_dev=None):
 # an empty one; one query head per KV head; a second wave of which only a remainder is split.
 @pytest.mark.parametrize("hq,hkv,d,n,c", [
     (32, 4, 128, [301], [9043]), (4, 1, 128, [2048], [0]), (8, 1, 128, [1], [16384]), (8, 2, 64, [65], [4097]),
-    (16, 2, 128, [33, 0, 257, 8], [5000, 7000, 3001, 12]), (8, 8, 64, [700], [2000]), (4, 4, 128, [256, 255], [2047, 3000]),
+    (16, 2, 128, [33, 0, 257, 8], [5000, 7000, 3001, 12]), (8, 8, 64, [700], [2000]),
+    (4, 4, 128, [256, 255], [2047, 3000]),
     (32, 4, 128, [560, 560, 560, 560], [6300, 6100, 6049, 5500])])
 def test_split_prefill_matches_oracle(kv, oracle_lib, hq, hkv, d, n, c):
     rng = np.random.default_rng(hq * 7 + n[0])
@@ -57,6 +58,32 @@ def test_split_prefill_matches_oracle(kv, oracle_lib, hq, hkv, d, n, c):
     whole, _, split = _call(kv, dp, q, None, None, n, c, tables, d, kv.PREFILL_COUNTER_BYTES)
     assert not split
     assert_attn_close(whole, ref, "unsplit prefill n=%s c=%s" % (n, c))
+    assert kv.ls_device_errors() == 0
+
+
+# Turns that end around the edges of a wave's 32 rows, a query tile and a key tile, where waves have
+# no rows or stop before the workgroup's last key tile (G = 1 and 8); and the same with one long turn,
+# where padding is a small share and every wave keeps to the workgroup's tiles.
+@pytest.mark.parametrize("mode", ["device", "host", "workspace"])
+@pytest.mark.parametrize("hq,hkv,d,n,c", [
+    (8, 8, 64, [31, 32, 33, 255, 256, 257, 1], [0, 0, 31, 0, 64, 63, 0]),
+    (4, 4, 128, [31, 33, 63, 65, 129, 255, 257, 300], [0, 1, 0, 64, 0, 15, 0, 100]),
+    (16, 2, 128, [3, 4, 5, 31, 33, 9], [0, 61, 64, 100, 0, 127]),
+    (2, 2, 64, [1700, 30], [0, 40])])
+def test_prefill_waves_without_rows_or_keys(kv, oracle_lib, hq, hkv, d, n, c, mode):
+    rng = np.random.default_rng(hkv + n[0])
+    n, c = np.array(n), np.array(c)
+    pool, tables, q, kn, vn = _case(rng, n, c, hq, hkv, d)
+    dp = DevicePool(kv, pool, d)
+    cu = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((kv.PREFILL_WORKSPACE_BYTES,), 0x5A, dtype=torch.uint8, device="cuda")
+    ws = ws if mode == "workspace" else None
+    kv.paged_attn_prefill(dp.pool, 0, bf16_dev(q), i32_dev(cu), i32_dev(c), int(n.max()), i32_dev(tables),
+                          1 / math.sqrt(d), out, bf16_dev(kn), bf16_dev(vn),
+                          lens_host=None if mode == "device" else np.stack([n, c], 1), workspace=ws)
+    ref = oracle_lib.prefill(pool, 16, d, 0, q, kn, vn, cu, c, tables, 1 / math.sqrt(d))
+    assert_attn_close(out, ref, "turns %s over %s" % (n, c))
     assert kv.ls_device_errors() == 0
 
 
