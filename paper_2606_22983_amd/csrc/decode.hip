@@ -185,11 +185,17 @@ __device__ __forceinline__ int attended_len(const DecodeArgs &a, int s, bool may
 }
 
 // Issue the loads of one block (blk < 0: a zero-size descriptor, nothing fetched).
-// koff, voff: this lane's byte offsets in k-step 0 and dim tile 0; the others
-// are constants further, kept in scalar registers.
-template <int D>
+// koff, voff: this lane's byte offsets, of every k-step and dim tile (arrays
+// of D / 32 and D / 16), or of the first ones alone, the others being constants
+// further in scalar registers.  The scalar form saves decode_small_kernel 11
+// registers; decode_kernel, which has them, keeps the arrays (with lengths on
+// the device: thinker call 134.5 against 139.1 us, talker step 110.4 against
+// 113.5).
+template <int D, int NK, int NV>
 __device__ __forceinline__ void load_block(BlockRegs<D> &r, const uint16_t *pool, int32_t num_kv_heads,
-                                           int32_t g, int32_t blk, int koff, int voff) {
+                                           int32_t g, int32_t blk, const int (&koff)[NK], const int (&voff)[NV]) {
+    static_assert((NK == D / 32 && NV == D / 16) || (NK == 1 && NV == 1), "every offset, or the first ones");
+    constexpr bool kAll = NV > 1;
     constexpr int kTileElems = kBlock * D;
     const bool valid = blk >= 0;
     const uint16_t *kt = pool + ((int64_t)(valid ? blk : 0) * 2 * num_kv_heads + g) * kTileElems;
@@ -198,9 +204,11 @@ __device__ __forceinline__ void load_block(BlockRegs<D> &r, const uint16_t *pool
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(kt), 0, bytes, kBufferDword3);
     const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(vt), 0, bytes, kBufferDword3);
 #pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) r.k[ks] = __builtin_amdgcn_raw_buffer_load_b128(rk, koff, ks * 4 * kBlock * 16, kStreamLoad);
+    for (int ks = 0; ks < D / 32; ++ks)
+        r.k[ks] = __builtin_amdgcn_raw_buffer_load_b128(rk, koff[kAll ? ks : 0], kAll ? 0 : ks * 4 * kBlock * 16, kStreamLoad);
 #pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) r.v[dt] = __builtin_amdgcn_raw_buffer_load_b64(rv, voff, dt * 16 * kBlock * 2, kStreamLoad);
+    for (int dt = 0; dt < D / 16; ++dt)
+        r.v[dt] = __builtin_amdgcn_raw_buffer_load_b64(rv, voff[kAll ? dt : 0], kAll ? 0 : dt * 16 * kBlock * 2, kStreamLoad);
 }
 
 // Online-softmax update with one 16-token block held in registers.
@@ -450,7 +458,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeArgs a, PlanA
     const int lane = tid % kWave;
     const int c16 = lane & 15;
     const int g4 = lane >> 4;
-    const int koff = (g4 * kBlock + c16) * 16, voff = (c16 * kBlock + g4 * 4) * 2;
+    int koff[D / 32], voff[D / 16];
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) koff[ks] = ((ks * 4 + g4) * kBlock + c16) * 16;   // = ks*1024 + lane*16
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt) voff[dt] = ((dt * 16 + c16) * kBlock + g4 * 4) * 2;
 
     // (session, split) of work row r of the device schedule.  A full row: the
     // largest s with sm_cum[s] <= r (a session without full splits shares its
@@ -876,7 +888,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_small_kernel(DecodeArgs a,
         const int b = __builtin_amdgcn_readlane(good, min(idx, kWave - 1));
         return idx < nblk ? b : -1;
     };
-    const int koff = (g4 * kBlock + c16) * 16, voff = (c16 * kBlock + g4 * 4) * 2;
+    const int koff[1] = {(g4 * kBlock + c16) * 16}, voff[1] = {(c16 * kBlock + g4 * 4) * 2};
     BlockRegs<D> r[kDepth];
     int bb[kDepth];
 #pragma unroll
