@@ -447,7 +447,8 @@ ls_status paged_attn_prefill(ls_kv_pool *pool, int32_t layer, int32_t num_sessio
                                              static_cast<const uint16_t *>(k_new),
                                              static_cast<const uint16_t *>(v_new), cu_new_lens,
                                              reused_lens, block_tables, max_blocks_per_session,
-                                             static_cast<uint32_t *>(workspace), err, stream);
+                                             lens_host ? static_cast<uint32_t *>(workspace) : nullptr, err,
+                                             stream);
         if (e != hipSuccess) return hip_fail(e, "append launch");
     }
     hipError_t e = launch_prefill(p, layer, num_sessions, num_q_heads, static_cast<const uint16_t *>(q),
