@@ -161,7 +161,7 @@ __device__ __forceinline__ float xsum16_32(float x) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// First key tile of part k of `parts` equal parts of ntiles key tiles.
+// First key tile of part k of `parts` equal parts of ntiles >= 0 key tiles.
 __device__ __forceinline__ int key_chunk(int ntiles, int k, int parts) { return (int)((unsigned)ntiles * (unsigned)k / (unsigned)parts); }
 
 // Entry jb of a session's block table, or -1 outside [0, nv).  The table does
@@ -304,8 +304,9 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
         // and key tiles are counted from tile0.
         int tile0 = 0, ntiles = (kv_end + kKeyTile - 1) / kKeyTile;
         if (kSplit && chunks > 1) {
-            tile0 = key_chunk(ntiles, chunk, chunks);
-            ntiles = key_chunk(ntiles, chunk + 1, chunks) - tile0;
+            const int all = max(ntiles, 0);                   // (a negative context, which is flagged, has no keys)
+            tile0 = key_chunk(all, chunk, chunks);
+            ntiles = key_chunk(all, chunk + 1, chunks) - tile0;
         }
         const int key_base = tile0 * kKeyTile;
         const int kv_len = c + n - key_base;

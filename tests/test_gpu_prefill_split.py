@@ -116,6 +116,22 @@ def test_split_prefill_with_other_device_lengths(kv, oracle_lib):
     kv.ls_device_errors()
 
 
+def test_split_prefill_with_a_negative_device_context(kv, oracle_lib):
+    """A device context below zero leaves every part of that session without key tiles: the call
+    ends, flags it, and the other session's rows are as usual."""
+    rng = np.random.default_rng(9)
+    n, c, d = np.array([200, 90]), np.array([5000, 4000]), 128
+    pool, tables, q, kn, vn = _case(rng, n, c, 16, 2, d)
+    ref = oracle_lib.prefill(pool, 16, d, 0, q, kn, vn, np.array([0, 200, 290]), c, tables, 1 / math.sqrt(d))
+    kv.ls_device_errors()
+    for c0 in (-1, -150, -300, -(1 << 30)):
+        dp = DevicePool(kv, pool, d)
+        out, _, split = _call(kv, dp, q, kn, vn, n, c, tables, d, kv.PREFILL_WORKSPACE_BYTES,
+                              lens_dev=(n, np.array([c0, 4000])))
+        assert split and kv.ls_device_errors() & kv.LS_DEVERR_LENGTH
+        assert_attn_close(out[200:], ref[200:], "beside a context of %d" % c0)
+
+
 def test_split_prefill_replays_from_a_graph(kv):
     rng = np.random.default_rng(8)
     n, c, d, hq, hkv = np.array([100]), np.array([8000]), 128, 32, 4
