@@ -310,7 +310,8 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
         }
         const int key_base = tile0 * kKeyTile;
         const int kv_len = c + n - key_base;
-        const int nb = min(nblk_valid - tile0 * 4, ntiles * 4);   // blocks any row here can see (none: <= 0)
+        int nb = min(nblk_valid - tile0 * 4, ntiles * 4);     // blocks any row here can see
+        if (kSplit) nb = max(nb, 0);                          // (a part past the end of the table)
 
         if (kSplit && chunks > 1 && ntiles <= 0) {             // a piece without keys
             for (int r = tid; r < kPreRows; r += kPreThreads) a.part_ml[((int64_t)piece * kPreRows + r) * 2] = kNoKey;

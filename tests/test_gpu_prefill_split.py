@@ -132,6 +132,24 @@ def test_split_prefill_with_a_negative_device_context(kv, oracle_lib):
         assert_attn_close(out[200:], ref[200:], "beside a context of %d" % c0)
 
 
+def test_split_prefill_with_device_contexts_past_the_table(kv):
+    """A device context longer than the table: flagged, and the blocks past the table are absent
+    (keys and values of zero) in whichever part they fall, as they are unsplit."""
+    rng = np.random.default_rng(10)
+    n, c, d = np.array([40, 60]), np.array([2000, 1900]), 128
+    pool, tables, q, kn, vn = _case(rng, n, c, 16, 2, d)
+    pool[(pool & 0x7FFF) > 0x7F80] = 0                        # (no NaN past the host's contexts)
+    dp = DevicePool(kv, pool, d)
+    for c0 in (2500, 8000, 20000):
+        dev = (n, np.array([c0, 1900]))
+        kv.ls_device_errors()
+        out, _, split = _call(kv, dp, q, kn, vn, n, c, tables, d, kv.PREFILL_WORKSPACE_BYTES, lens_dev=dev)
+        assert split and kv.ls_device_errors() & kv.LS_DEVERR_LENGTH
+        whole, _, split = _call(kv, dp, q, kn, vn, n, c, tables, d, kv.PREFILL_COUNTER_BYTES, lens_dev=dev)
+        assert not split and kv.ls_device_errors() & kv.LS_DEVERR_LENGTH
+        assert_attn_close(out, whole.float().cpu().numpy(), "context of %d in a table of %d" % (c0, 16 * tables.shape[1]))
+
+
 def test_split_prefill_replays_from_a_graph(kv):
     rng = np.random.default_rng(8)
     n, c, d, hq, hkv = np.array([100]), np.array([8000]), 128, 32, 4
