@@ -77,7 +77,7 @@ constexpr int kXcds = kPrefillCounters;                 // workgroups are dispat
 constexpr int kMaxPairs = 512;           // (session, KV head) pairs scheduled; more run in index order
 constexpr int kPlanPairs = 256;          // entries (and pairs, and sessions) a host-dealt schedule holds
 constexpr int kSplitItems = kPrefillSplitPieces / 2;   // query tiles that can be split (two pieces at least)
-constexpr float kNoKey = -INFINITY;      // a piece's running max for a row that sees none of its keys
+constexpr float kNoKey = -INFINITY;      // a piece's running max for a row that none of its keys adds to
 
 struct PrefillArgs {
     const uint16_t *pool;          // layer base
@@ -631,6 +631,53 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
             nm[rt] = -xmax16_32(lane_max(sa[rt])) * sl2;
             if (kSplit && row_lim[rt] < 0) nm[rt] = 0.f;
         }
+        // A row whose scores in the first unit are all -inf has no maximum to
+        // start from: -inf - (-inf) is NaN, and a stand-in far below the scores
+        // to come would cost them their low bits.  Any part can begin so, not
+        // only the context; the row starts from its first unit that holds more,
+        // found here with K straight from the pool (rare).  Without one its
+        // probabilities are 0.
+        if constexpr (kSplit) {
+            auto lost = [&] {
+                bool any = false;
+    #pragma unroll
+                for (int rt = 0; rt < kRT; ++rt) any = any || nm[rt] == INFINITY;
+                return __any(any);
+            };
+            if (lost()) {
+                for (int u = 1; u < 2 * wave_tiles && lost(); ++u) {
+                    const int32_t b0 = table_entry(table, 2 * u, nb), b1 = table_entry(table, 2 * u + 1, nb);
+                    const uint32_t b = (uint32_t)(c16 >> 3 ? b1 : b0);
+                    const bool there = b < nblocks32;
+                    const uint16_t *kt = kbase + (uint64_t)(there ? b : 0u) * slab_elems;
+                    f32x4 acc[kRT][2];
+    #pragma unroll
+                    for (int sb = 0; sb < 2; ++sb) {
+                        const int t = 8 * ((c16 >> 2) & 1) + 4 * sb + (c16 & 3);
+    #pragma unroll
+                        for (int rt = 0; rt < kRT; ++rt) acc[rt][sb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    #pragma unroll
+                        for (int ks = 0; ks < KS; ++ks) {
+                            const u32x4 raw = *reinterpret_cast<const u32x4 *>(kt + ((ks * 4 + g4) * kBlock + t) * 8);
+                            const bf16x8 kv = __builtin_bit_cast(bf16x8, there ? raw : u32x4{0u, 0u, 0u, 0u});
+    #pragma unroll
+                            for (int rt = 0; rt < kRT; ++rt)
+                                acc[rt][sb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv, qop[rt][ks], acc[rt][sb], 0, 0, 0);
+                        }
+                    }
+                    mask_unit(acc, u * 32);
+    #pragma unroll
+                    for (int rt = 0; rt < kRT; ++rt) {
+                        const float first = -xmax16_32(lane_max(acc[rt])) * sl2;
+                        if (nm[rt] == INFINITY) nm[rt] = first;
+                    }
+                }
+    #pragma unroll
+                for (int rt = 0; rt < kRT; ++rt)
+                    if (nm[rt] == INFINITY) nm[rt] = 0.f;
+                read_k(k0);                   // again: not kept in registers across the search
+            }
+        }
         scale_unit(sa);
         __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the zeros are written
         asm volatile("" ::: "memory");
@@ -700,7 +747,8 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
             for (int rt = 0; rt < kRT; ++rt) {
                 const float l = xsum16_32(lsum[rt]);
                 if (g4 == 0) {
-                    ml[rt * 32] = row_lim[rt] < 0 ? kNoKey : -nm[rt];
+                    // (a zero sum: every score of the row here is -inf)
+                    ml[rt * 32] = row_lim[rt] < 0 || l == 0.f ? kNoKey : -nm[rt];
                     ml[rt * 32 + 1] = l;
                 }
     #pragma unroll
@@ -714,7 +762,13 @@ __global__ __launch_bounds__(kPreThreads) void prefill_kernel(PrefillArgs a, Pre
         for (int rt = 0; rt < kRT; ++rt) {
             const float inv = 1.f / xsum16_32(lsum[rt]);
             if (!row_ok[rt]) continue;
-            uint16_t *orow = a.out + row_out[rt];
+            int64_t at = row_out[rt];
+            if constexpr (kSplit) {                            // derived again: 64 bits less to keep through the loop
+                int r = wave * kWaveRows + rt * 16 + c16;
+                asm volatile("" : "+v"(r));
+                at = (((int64_t)a.cu[s] + j0 + r / G) * hq_total + g * G + r % G) * D;
+            }
+            uint16_t *orow = a.out + at;
     #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) {
                 const u32x2 w = u32x2{pack_bf16x2(o[rt][dt][0] * inv, o[rt][dt][1] * inv),
@@ -942,8 +996,7 @@ __global__ __launch_bounds__(kMergeThreads) void prefill_merge_kernel(PrefillArg
         acc *= keep;
 #pragma unroll
         for (int i = 0; i < kMergePre; ++i) {
-            // (An empty piece's sums and output were not written; a row without
-            // keys in a piece has zeros.)
+            // (An empty piece's sums and output were not written.)
             const bool seen = k0 + i < chunks && m[i] != kNoKey;
             const float w = seen ? __builtin_amdgcn_exp2f(m[i] - Mn) : 0.f;
             L += seen ? w * l[i] : 0.f;

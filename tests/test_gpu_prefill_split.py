@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2606_22983_amd import workloads as W
 from tests.gpu_util import DevicePool, assert_attn_close, bf16_dev, i32_dev, scale_keys
 from tests.test_gpu_prefill import _case
 
@@ -85,6 +86,52 @@ def test_prefill_waves_without_rows_or_keys(kv, oracle_lib, hq, hkv, d, n, c, mo
     ref = oracle_lib.prefill(pool, 16, d, 0, q, kn, vn, cu, c, tables, 1 / math.sqrt(d))
     assert_attn_close(out, ref, "turns %s over %s" % (n, c))
     assert kv.ls_device_errors() == 0
+
+
+# Keys whose scores overflow to -inf for the rows with q[0] = 8, and are ordinary for those with q[0] = 0
+# (8 * -3e38 is past the fp32 range): the first 32 keys of every key tile but the first, so that every
+# part after the first begins with them; a run of key tiles that holds whole parts; everything but the
+# first key tile and the turn itself.
+@pytest.mark.parametrize("where", ["unit", "parts", "rest"])
+@pytest.mark.parametrize("hq,hkv,d,n,c", [(16, 2, 128, [40], [6000]), (8, 2, 64, [65, 3], [4097, 2500]),
+                                          (4, 4, 128, [300], [3000])])
+def test_split_prefill_of_scores_that_overflow(kv, oracle_lib, hq, hkv, d, n, c, where):
+    rng = np.random.default_rng(11)
+    n, c = np.array(n), np.array(c)
+    pool, tables, q, kn, vn = _case(rng, n, c, hq, hkv, d)
+    for s in range(len(n)):
+        t = np.arange(int(c[s]))
+        t = t[{"unit": (t >= 64) & (t % 64 < 32), "parts": (t >= 640) & (t < 640 + 64 * ((c[s] - 700) // 64)),
+               "rest": t >= 64}[where]]
+        pool[0, tables[s, t // 16], 0, :, (t % 16) * 8] = W.to_bf16(np.float32(-3e38))      # dim 0 of the K rows
+    q[:, :, 0] = 0
+    q[::2, :, 0] = W.to_bf16(np.float32(8.0))
+    dp = DevicePool(kv, pool, d)
+    out, cu, split = _call(kv, dp, q, kn, vn, n, c, tables, d, kv.PREFILL_WORKSPACE_BYTES)
+    ref = oracle_lib.prefill(pool, 16, d, 0, q, kn, vn, cu, c, tables, 1 / math.sqrt(d))
+    assert split
+    assert_attn_close(out, ref, "%s of scores at -inf" % where)
+    whole, _, split = _call(kv, dp, q, None, None, n, c, tables, d, kv.PREFILL_COUNTER_BYTES)
+    assert not split
+    assert_attn_close(whole, ref, "%s of scores at -inf, unsplit" % where)
+    assert kv.ls_device_errors() == 0
+
+
+@pytest.mark.parametrize("bits", [0x7FC0, 0x7F80])
+def test_split_prefill_of_nan_and_inf_keys(kv, oracle_lib, bits):
+    """A NaN key, or one whose score is +inf, late in the context: the rows that are NaN unsplit are
+    NaN, the others as without it."""
+    rng = np.random.default_rng(12)
+    n, c, d = np.array([40]), np.array([6000]), 128
+    pool, tables, q, kn, vn = _case(rng, n, c, 16, 2, d)
+    q[:, :, 0] = W.to_bf16(np.float32(1.0))
+    ref = oracle_lib.prefill(pool, 16, d, 0, q, kn, vn, np.array([0, 40]), c, tables, 1 / math.sqrt(d))
+    pool[0, tables[0, 4000 // 16], 0, 1, (4000 % 16) * 8] = bits                 # KV head 1 alone
+    dp = DevicePool(kv, pool, d)
+    out, _, split = _call(kv, dp, q, kn, vn, n, c, tables, d, kv.PREFILL_WORKSPACE_BYTES)
+    whole, _, _ = _call(kv, dp, q, None, None, n, c, tables, d, kv.PREFILL_COUNTER_BYTES)
+    assert split and torch.equal(out.isnan(), whole.isnan()) and bool(out[:, 8:].isnan().all())
+    assert_attn_close(out[:, :8], ref[:, :8], "beside a key of %#x" % bits)
 
 
 @pytest.mark.parametrize("shape", ["rising", "spike", "falling"])
