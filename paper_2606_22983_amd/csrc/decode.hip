@@ -94,7 +94,7 @@ struct DecodeArgs {
     float *part_acc;               // [S][Hkv][max_splits][G][D]
     unsigned int *err;             // device error word
     int32_t num_sessions;
-    uint64_t *arrived;             // decode_small_kernel: [S][Hkv] arrival counts (kArrivedTag | count)
+    uint64_t *arrived;             // decode_small_kernel: [S][Hkv] arrival counts (arrived_word)
 };
 
 // A schedule planned on the host (paged_attn_decode with host lengths),
@@ -742,29 +742,45 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeArgs a, PlanA
 // of which 252 had keys, started its last ones 26 us into the call.)
 //
 // The finishing order is taken from a 64-bit count per (session, KV head) in
-// the workspace, whose contents on entry are arbitrary: a word counts only if
-// its upper 48 bits are the tag.  A split adds 1; if the word it found was
-// tagged, it was the count; otherwise the word is replaced (compare-and-swap)
-// by the tag and a first count, or, when another split has just done so, the
-// add is made again on the tagged word.  The last one leaves tag | 0.  A
-// stray word equal to a tag with a nonzero count cannot be left by a finished
-// call, and by chance has odds of 2^-48 per word.
-constexpr uint64_t kArrivedTag = 0x9D3B6E52C1A70000ull;
-constexpr uint64_t kArrivedMask = 0xFFFFull;
+// the workspace, whose contents on entry are arbitrary: no finished call, other
+// use of the memory or part of a word written over may leave what looks like a
+// count on the way.  So the count n stands in the word twice, as n under one
+// tag in the low half and as ~n under another in the high half, and only a word
+// whose halves agree on an n below the session's splits is a count.  A split
+// adds 1 to the low and -1 to the high half at once; if the word it found was a
+// count, that was the order; otherwise the word is replaced (compare-and-swap)
+// by a first count, or, when another split has just done so, the add is made
+// again.  The last one leaves 0.  Adds to other words can make a count of one
+// only by carrying into both tags at once, and that count is 0, with every
+// split that added before still to add again.  A store of up to four bytes
+// changes one half, so it leaves either the same word or no count.  Both tags
+// are signalling NaNs as floats, which no arithmetic returns, so partials never
+// read as counts either; other 64-bit values do with odds of 2^-48.
+constexpr uint32_t kArrivedLow = 0xFFB50000u, kArrivedHigh = 0xFF9A0000u;
+constexpr uint64_t kArrivedAdd = 0xFFFFFFFF00000001ull;
 constexpr int kArrivedStride = 16;           // words from one count to the next: a cache line each
 
-__device__ __forceinline__ unsigned count_arrival(uint64_t *word) {
-    uint64_t old = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    while ((old & ~kArrivedMask) != kArrivedTag) {
+__device__ __forceinline__ uint64_t arrived_word(uint32_t n) {
+    return (uint64_t)(kArrivedHigh | (~n & 0xFFFFu)) << 32 | kArrivedLow | n;
+}
+// The count a word holds, or -1.
+__device__ __forceinline__ int arrived_count(uint64_t word, int nsplit) {
+    const int n = (int)(word & 0xFFFFu);
+    return n < nsplit && word == arrived_word((uint32_t)n) ? n : -1;
+}
+
+__device__ __forceinline__ int count_arrival(uint64_t *word, int nsplit) {
+    uint64_t old = __hip_atomic_fetch_add(word, kArrivedAdd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (arrived_count(old, nsplit) < 0) {
         uint64_t cur = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((cur & ~kArrivedMask) == kArrivedTag) {
-            old = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else if (__hip_atomic_compare_exchange_strong(word, &cur, kArrivedTag | 1ull, __ATOMIC_RELAXED,
+        if (arrived_count(cur, nsplit) >= 0) {
+            old = __hip_atomic_fetch_add(word, kArrivedAdd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else if (__hip_atomic_compare_exchange_strong(word, &cur, arrived_word(1), __ATOMIC_RELAXED,
                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-            old = kArrivedTag;
+            old = arrived_word(0);
         }
     }
-    return (unsigned)(old & kArrivedMask);
+    return arrived_count(old, nsplit);
 }
 
 // Partials and counts cross XCDs, whose L2s are not coherent, so they are read
@@ -802,7 +818,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_small_kernel(DecodeArgs a,
     __shared__ float sm_m[kDecWaves][kMaxGroup];
     __shared__ float sm_l[kDecWaves][kMaxGroup];
     __shared__ __attribute__((aligned(16))) float sm_o[kDecWaves][kMaxGroup][D];
-    __shared__ unsigned sm_before;
+    __shared__ int sm_before;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lane = tid % kWave;
@@ -963,11 +979,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_small_kernel(DecodeArgs a,
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0): this wave's partials are on their way out
         __syncthreads();
-        if (tid == 0) sm_before = count_arrival(count);
+        if (tid == 0) sm_before = count_arrival(count, nsplit);
         __syncthreads();
-        if ((int)sm_before != nsplit - 1) return;
+        if (sm_before != nsplit - 1) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if (tid == 0) __hip_atomic_store(count, kArrivedTag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_store(count, arrived_word(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (active) {
             const float *pm = a.part_ml + (part * G + h) * 2;
             const float *pa = a.part_acc + part * G * D + base;

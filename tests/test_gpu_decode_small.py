@@ -2,6 +2,8 @@
 finish, without a second launch.  Against the oracle at the edges of blocks, splits and rows, with
 arbitrary workspace contents."""
 import math
+import os
+import re
 
 import numpy as np
 import pytest
@@ -36,6 +38,18 @@ def _call(kv, dp, q, kn, vn, tables, lens, host, ws, d, lens_host=None):
     return out
 
 
+def _tag(name):
+    """A constant of the kernel's source."""
+    src = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2606_22983_amd", "csrc")
+    return int(re.search(r"\b%s = (0x[0-9A-F]+)u" % name, open(os.path.join(src, "decode.hip")).read()).group(1), 16)
+
+
+def _arrived(n, below=0):
+    """An arrival word of count n (n = 0, below > 0: a word that `below` arrivals turn into one), as int64."""
+    low, high = _tag("kArrivedLow") + n - below, _tag("kArrivedHigh") + (0xFFFF - n) + below
+    return (high << 32 | low) - (1 << 64)
+
+
 def _workspace(kv, dp, q, tables, fill):
     n = kv.decode_workspace_bytes(dp.pool, q.shape[0], q.shape[1], tables.shape[1])
     ws = torch.empty((n + 7) // 8, dtype=torch.int64, device="cuda")
@@ -63,10 +77,12 @@ def test_small_decode_matches_oracle(kv, oracle_lib, hq, hkv, d, lens, append, h
     assert _small(kv, dp, q, tables, lens, append, host)
     ref, ref_pool = oracle_lib.decode(pool, 16, d, 0, q, tables, lens, 1 / math.sqrt(d), k_new=kn, v_new=vn,
                                       pool_out=True)
-    # Arbitrary contents of the counts: zeros, ones, a word one below the tag's, what the call leaves.
+    # Arbitrary contents of the counts: zeros, ones, words that arrivals carry into a count, counts past
+    # any call's splits, what the call leaves.
     ws = _workspace(kv, dp, q, tables, 0)
     first = None
-    for fill in (0, -1, 0x1D3B6E52C1A6FFFF, 0x3F8000003F800000, None, None):
+    for fill in (0, -1, 0x3F8000003F800000, _arrived(0, 1), _arrived(0, 2), _arrived(0, 3), _arrived(300),
+                 _arrived(0xFFFF), None, None):
         if fill is not None:
             ws.fill_(fill)
         out = _call(kv, dp, q, kn, vn, tables, lens, host, ws, d)
@@ -80,6 +96,29 @@ def test_small_decode_matches_oracle(kv, oracle_lib, hq, hkv, d, lens, append, h
     n = kv.decode_workspace_bytes(dp.pool, len(lens), hq, tables.shape[1])
     other = _call(kv, dp, q, kn, vn, tables, lens, host, torch.zeros(n // 8 + 2, dtype=torch.int64, device="cuda")[1:], d)
     assert_attn_close(other, ref, "8-byte aligned workspace")
+    assert kv.ls_device_errors() == 0
+
+
+@pytest.mark.parametrize("host", [False, True])
+def test_small_decode_after_part_of_a_count_was_overwritten(kv, oracle_lib, host):
+    """The memory of a finished call's workspace goes to other use, of which stores of one, two or four
+    bytes reach the counts, and comes back as a workspace."""
+    rng = np.random.default_rng(13)
+    lens = np.array([513, 3000, 1, 767, 1600])
+    pool, tables, q, _, _ = _synthetic(rng, lens, 16, 2, 128, False)
+    dp = DevicePool(kv, pool, 128)
+    assert _small(kv, dp, q, tables, lens, False, host)
+    ref = oracle_lib.decode(pool, 16, 128, 0, q, tables, lens, 1 / math.sqrt(128))
+    ws = _workspace(kv, dp, q, tables, 0)
+    first = _call(kv, dp, q, None, None, tables, lens, host, ws, 128)
+    assert_attn_close(first, ref, "small decode")
+    for dtype, size in ((torch.uint8, 1), (torch.int16, 2), (torch.int32, 4)):
+        for at in range(0, 8, size):
+            for value in (0, 1, 2, 255 if size == 1 else -1):
+                ws.view(dtype)[at // size::128 // size] = value
+                ws.view(torch.uint8)[len(lens) * 2 * 128:] = 0xFF                 # no partials of an earlier call
+                out = _call(kv, dp, q, None, None, tables, lens, host, ws, 128)
+                assert torch.equal(out.view(torch.int16), first.view(torch.int16)), (size, at, value)
     assert kv.ls_device_errors() == 0
 
 
