@@ -784,14 +784,25 @@ __device__ __forceinline__ int count_arrival(uint64_t *word, int nsplit) {
 }
 
 // Partials and counts cross XCDs, whose L2s are not coherent, so they are read
-// and written with device-scope accesses: such a store goes through to the
-// point where every XCD reads, and the wave's vmcnt counts it only once it is
-// there; such a load misses the reader's L2.  So: every wave stores, waits for
-// vmcnt(0) and meets the workgroup's barrier before one thread adds to the
-// count, and the workgroup that finds the count complete loads after its own
-// barrier.  An agent-scope release and acquire around the count order the same
-// accesses by writing back and invalidating whole L2s, once per workgroup:
-// measured 1 us more on 28 workgroups and 40 against 25 us on 544.
+// and written with device-scope atomic accesses and no others: every wave
+// stores, waits (wait_device_stores) and meets the workgroup's barrier before
+// one thread adds to the count, and the workgroup that finds the count complete
+// loads after its own barrier.
+// Why the wait is enough: in LLVM's memory model for gfx942, which gfx950
+// shares (User Guide for AMDGPU Backend, "Memory Model GFX942", table of code
+// sequences), atomic loads and stores of agent scope carry sc1, so they are
+// performed where all L2s of the agent agree; a release of agent scope is
+// buffer_wbl2 sc1, which writes back what ordinary stores left in the L2, and
+// s_waitcnt vmcnt(0), which holds the releasing access until every earlier one
+// has completed; an acquire is the wait for the acquiring access, and
+// buffer_inv sc1, which drops lines that ordinary loads could hit.  Without
+// ordinary accesses the two waits are what is left of it.  (A wave's loads
+// behind a branch are not issued before the branch is taken.)
+// The compiler may move relaxed accesses of other addresses across a wait
+// builtin, but none across the asm statement, which clobbers memory.
+// Measured with agent-scope release and acquire fences around the count
+// instead: 1 us more on 28 workgroups and 40 against 25 us on 544.
+__device__ __forceinline__ void wait_device_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void store_device(float *p, float x, float y) {
     const u32x2 w = {__float_as_uint(x), __float_as_uint(y)};
     __hip_atomic_store(reinterpret_cast<uint64_t *>(p), __builtin_bit_cast(uint64_t, w), __ATOMIC_RELAXED,
@@ -977,7 +988,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_small_kernel(DecodeArgs a,
             store_device(po + 2, acc[2], acc[3]);
             if (d == 0) store_device(a.part_ml + ((int64_t)blockIdx.x * G + h) * 2, M, wsum);
         }
-        __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0): this wave's partials are on their way out
+        wait_device_stores();
         __syncthreads();
         if (tid == 0) sm_before = count_arrival(count, nsplit);
         __syncthreads();
