@@ -67,10 +67,10 @@ struct DecodePlan {
     size_t total() const { return ml_bytes + acc_bytes; }            // the least a call takes
     size_t recommended() const { return total() > small_bytes ? total() : small_bytes; }
 };
-// lens_host null: every session may be as long as its table.  bytes: room for
-// counts and partials.
-SmallDecodePlan plan_small(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads, int32_t max_blocks,
-                           const int32_t *lens_host, int32_t appended, size_t bytes);
+// lens_host null: every session may be as long as its table.  cus: CUs of the
+// stream.  bytes: room for counts and partials.
+SmallDecodePlan plan_small(const PoolGeom &p, int64_t cus, int32_t num_sessions, int32_t num_q_heads,
+                           int32_t max_blocks, const int32_t *lens_host, int32_t appended, size_t bytes);
 DecodePlan plan_decode(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads,
                        int32_t max_blocks_per_session);
 

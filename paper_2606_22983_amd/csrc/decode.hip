@@ -1129,8 +1129,8 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(DecodeArgs
 
 }  // namespace
 
-// Batches that decode_small_kernel takes: those whose workgroups are resident
-// at once (device lengths are taken as uniform up to the table's width).
+// Batches that decode_small_kernel takes: those whose workgroups are few per
+// CU (device lengths are taken as uniform up to the table's width).
 // Splits of 256 tokens (two blocks per wave), 512, 768 or 1024 tokens; at
 // D = 64 of 512 or 1024: all of a wave's blocks are in flight at once up to
 // 512 tokens, two (four) at a time beyond.  Other lengths cost what the next of
@@ -1146,16 +1146,24 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(DecodeArgs
 // (session, KV head) has one workgroup, and any number of them is taken (200
 // sessions of 50-300 keys at 4 heads 37.6 -> 25.3 us, 64 of 300-900 with device
 // lengths 30.2 -> 20.8).
+// At D = 128 the CUs are the stream's.  On a stream of 24 of the 256 CUs, with
+// splits chosen for 256 against the persistent kernel: one session of 16,000
+// keys 52.1 and 37.4 us, 8 of up to 16k 144 and 122, 16 of 300-2500 75.7 and
+// 52.6.  At D = 64 they are the device's: two workgroups of 89 registers fit a
+// CU and the third waits for a place, and still, with device lengths, this
+// kernel is the faster at any number of them (48 sessions of 100-3000 keys, 652
+// workgroups: 24.6 -> 19.9 us on 256 CUs, 33.1 -> 26.3 on 128, 145 -> 108 on 24).
 struct SmallSize {
     int tokens, per_cu;
 };
 constexpr SmallSize kSmallSizes128[] = {{256, 1}, {512, 1}, {256, 2}, {768, 1}, {1024, 1}};
 constexpr SmallSize kSmallSizes64[] = {{512, 3}, {1024, 1}};
 
-SmallDecodePlan plan_small(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads, int32_t max_blocks,
-                           const int32_t *lens_host, int32_t appended, size_t bytes) {
+SmallDecodePlan plan_small(const PoolGeom &p, int64_t cus, int32_t num_sessions, int32_t num_q_heads,
+                           int32_t max_blocks, const int32_t *lens_host, int32_t appended, size_t bytes) {
     const SmallDecodePlan none;
-    const int64_t cus = p.num_cus > 0 ? p.num_cus : 256, hkv = p.num_kv_heads;
+    const int64_t hkv = p.num_kv_heads;
+    if (p.head_dim != 128) cus = p.num_cus > 0 ? p.num_cus : 256;
     if (num_sessions > kMaxBatch) return none;
     int64_t longest = (int64_t)max_blocks * kBlock;
     if (lens_host) {
@@ -1240,7 +1248,7 @@ DecodePlan plan_decode(const PoolGeom &p, int32_t num_sessions, int32_t num_q_he
         const int64_t shortest = p.head_dim == 128 ? kSmallSizes128[0].tokens : kSmallSizes64[0].tokens;
         const int64_t wgs = std::min(3 * cus, sg * ((max_tokens + shortest - 1) / shortest));
         const size_t most = pad((size_t)wgs * G * (p.head_dim + 2) * sizeof(float)) + 512;
-        const SmallDecodePlan dev = plan_small(p, num_sessions, num_q_heads, max_blocks_per_session, nullptr, 0, SIZE_MAX);
+        const SmallDecodePlan dev = plan_small(p, cus, num_sessions, num_q_heads, max_blocks_per_session, nullptr, 0, SIZE_MAX);
         plan.small_bytes = std::max(dev.total(), (size_t)sg * kArrivedStride * sizeof(uint64_t) + most);
     }
     return plan;
@@ -1502,8 +1510,8 @@ const CachedPlan *cached_decode_plan(int S, int hkv, const int32_t *lens_host, i
 DecodeSchedule decode_schedule(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads, int32_t max_blocks,
                                const int32_t *context_lens_host, int32_t appended, const DecodePlan &plan,
                                hipStream_t stream) {
-    const SmallDecodePlan sp =
-        plan_small(p, num_sessions, num_q_heads, max_blocks, context_lens_host, appended, plan.recommended());
+    const SmallDecodePlan sp = plan_small(p, stream_cus(p, stream), num_sessions, num_q_heads, max_blocks,
+                                          context_lens_host, appended, plan.recommended());
     if (sp.split_tokens) return DecodeSchedule{sp.split_tokens, context_lens_host != nullptr, false};
     DecodeSchedule sc{plan.split_tokens, false, plan.max_splits > 1};
     if (context_lens_host) {
@@ -1545,8 +1553,9 @@ hipError_t launch_decode(const PoolGeom &p, int layer, int32_t num_sessions, int
     a.arrived = nullptr;
     // Small batches.  The room is the query's, so that the same call gives the
     // same result from any workspace of at least that size.
-    const SmallDecodePlan sp = plan_small(p, num_sessions, num_q_heads, max_blocks, context_lens_host, a.appended,
-                                          std::min(workspace_bytes, plan.recommended()));
+    const int64_t resident = (int64_t)stream_cus(p, stream);
+    const SmallDecodePlan sp = plan_small(p, resident, num_sessions, num_q_heads, max_blocks, context_lens_host,
+                                          a.appended, std::min(workspace_bytes, plan.recommended()));
     if (sp.split_tokens && (sp.single || reinterpret_cast<uintptr_t>(workspace) % 16 == 0)) {
         a.split_tokens = sp.split_tokens;
         a.max_splits = sp.single ? 1 : 0;
@@ -1582,7 +1591,6 @@ hipError_t launch_decode(const PoolGeom &p, int layer, int32_t num_sessions, int
 #undef LS_SMALL
         return hipGetLastError();
     }
-    const int64_t resident = (int64_t)stream_cus(p, stream);
     dim3 cgrid(p.num_kv_heads, num_sessions);
     // Host lengths: the schedule is planned here and passed with the arguments.
     if (context_lens_host) {

@@ -1,12 +1,16 @@
 """Kernels on CU-masked streams: the persistent grids are sized to the CUs the
 stream may use, and the results do not depend on it."""
+import math
+
 import numpy as np
 import pytest
 import torch
 
 from paper_2606_22983_amd import workloads as W
-from tests.gpu_util import (DevicePool, bf16_dev, cu_masked_stream, destroy_stream, host_bits,
+from tests.gpu_util import (DevicePool, assert_attn_close, bf16_dev, cu_masked_stream, destroy_stream, host_bits,
                             i32_dev, log)
+from tests.test_gpu_decode import _synthetic
+from tests.test_gpu_prefill import _case
 
 pytestmark = pytest.mark.gpu
 
@@ -51,6 +55,75 @@ def test_decode_on_cu_masked_stream_is_bit_identical(kv, lo, hi):
     finally:
         torch.cuda.synchronize()
         destroy_stream(handle)
+
+
+@pytest.mark.parametrize("host", [False, True])
+@pytest.mark.parametrize("hq,hkv,d,lens", [
+    (32, 4, 128, [9000]), (16, 2, 128, [300, 2500, 1, 1200, 900, 2000]), (32, 4, 128, [700] * 6), (16, 4, 64, [100, 3000, 513]),
+    (8, 8, 64, [500, 40, 512])])
+def test_small_decode_on_cu_masked_streams(kv, oracle_lib, hq, hkv, d, lens, host):
+    """Small batches on streams of 8, 24 and 128 CUs in turn, one workspace: the split size, and the
+    kernel, follow the stream's CUs at D = 128, and the results are the oracle's on each."""
+    rng = np.random.default_rng(len(lens) + d)
+    lens = np.array(lens)
+    pool, tables, q, _, _ = _synthetic(rng, lens, hq, hkv, d, False)
+    dp = DevicePool(kv, pool, d)
+    ref = oracle_lib.decode(pool, 16, d, 0, q, tables, lens, 1 / math.sqrt(d))
+    ws = torch.full((kv.decode_workspace_bytes(dp.pool, len(lens), hq, tables.shape[1]),), 0x5A, dtype=torch.uint8,
+                    device="cuda")
+    qd, td, ld = bf16_dev(q), i32_dev(tables), i32_dev(lens)
+    merges = []
+    for hi in (8, 24, 128, 8):
+        made = cu_masked_stream(0, hi)
+        if made is None:
+            pytest.skip("runtime has no hipExtStreamCreateWithCUMask")
+        stream, handle = made
+        try:
+            out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+            torch.cuda.synchronize()
+            kv.paged_attn_decode(dp.pool, 0, qd, td, ld, 1 / math.sqrt(d), out, ws, stream=stream,
+                                 context_lens_host=lens if host else None)
+            stream.synchronize()
+            assert_attn_close(out, ref, "small decode on %d CUs" % hi)
+            merges.append(kv.ls_decode_schedule(dp.pool, len(lens), hq, tables.shape[1], lens if host else None,
+                                                stream=stream)["merge"])
+        finally:
+            torch.cuda.synchronize()
+            destroy_stream(handle)
+    assert kv.ls_device_errors() == 0
+    # 9 to 18 splits of 9000 keys at 4 heads are few on 128 CUs, and too many on 8
+    if len(lens) == 1:
+        assert not kv.ls_decode_schedule(dp.pool, 1, hq, tables.shape[1], lens if host else None)["merge"]
+        assert merges[0] and merges[3] and not merges[2]
+
+
+def test_split_prefill_on_cu_masked_stream(kv, oracle_lib):
+    """A turn whose keys are split by the stream's CUs (24 of them, and 200)."""
+    rng = np.random.default_rng(21)
+    n, c, d = np.array([150, 20]), np.array([6000, 3000]), 128
+    pool, tables, q, kn, vn = _case(rng, n, c, 16, 2, d)
+    cu = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    ref = oracle_lib.prefill(pool, 16, d, 0, q, kn, vn, cu, c, tables, 1 / math.sqrt(d))
+    dp = DevicePool(kv, pool, d)
+    args = [bf16_dev(q), i32_dev(cu), i32_dev(c), 150, i32_dev(tables), 1 / math.sqrt(d)]
+    new = [bf16_dev(kn), bf16_dev(vn)]
+    for lo, hi in ((0, 24), (40, 240)):
+        made = cu_masked_stream(lo, hi)
+        if made is None:
+            pytest.skip("runtime has no hipExtStreamCreateWithCUMask")
+        stream, handle = made
+        try:
+            out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+            ws = torch.full((kv.PREFILL_WORKSPACE_BYTES,), 0xFF, dtype=torch.uint8, device="cuda")
+            torch.cuda.synchronize()
+            kv.paged_attn_prefill(dp.pool, 0, *args, out, *new, lens_host=np.stack([n, c], 1), workspace=ws, stream=stream)
+            stream.synchronize()
+            assert not bool((ws[kv.PREFILL_COUNTER_BYTES:] == 0xFF).all())        # something was split
+            assert_attn_close(out, ref, "split prefill on CUs %d..%d" % (lo, hi - 1))
+        finally:
+            torch.cuda.synchronize()
+            destroy_stream(handle)
+    assert kv.ls_device_errors() == 0
 
 
 def test_restore_on_cu_masked_stream_is_bit_exact(kv):
