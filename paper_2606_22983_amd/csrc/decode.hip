@@ -1505,13 +1505,39 @@ const CachedPlan *cached_decode_plan(int S, int hkv, const int32_t *lens_host, i
     return &c;
 }
 
+// plan_small for a call on a stream of `cus` CUs.  At D = 64 with host lengths
+// the persistent kernel keeps the batches that its host plan runs without a
+// merge, one item per (session, KV head), when split ones would come to more
+// than a workgroup per CU (more than two, if whole sessions come to more than
+// one): the last splits are mostly padding.  28 such batches: 24 are faster
+// whole, by up to 21% (63 sessions of 1100-1200 keys at 4 heads 16.3 us, 20.7
+// split; 47 of 1700 17.8 and 21.4), four slower, one of them by 17%.  The split
+// form is kept where it is the faster one: with at most a workgroup per CU (16
+// batches, 0.98 to 1.15 times as fast), up to two of sessions that already come
+// to more than one (9 batches, 0.95 to 1.30), and wherever the host plan merges
+// (20 batches of 96 to 768 workgroups, 1.25 to 1.66).
+SmallDecodePlan plan_small_call(const PoolGeom &p, int64_t cus, int32_t num_sessions, int32_t num_q_heads,
+                                int32_t max_blocks, const int32_t *lens_host, int32_t appended, size_t bytes,
+                                const DecodePlan &plan) {
+    const SmallDecodePlan sp = plan_small(p, cus, num_sessions, num_q_heads, max_blocks, lens_host, appended, bytes);
+    if (!sp.split_tokens || sp.single || p.head_dim == 128 || !lens_host) return sp;
+    const int64_t whole = (int64_t)num_sessions * p.num_kv_heads, split = (int64_t)sp.rows * p.num_kv_heads;
+    if (split > (whole <= cus ? cus : 2 * cus)) {
+        const CachedPlan *c = cached_decode_plan(num_sessions, p.num_kv_heads, lens_host, appended, (int)cus,
+                                                 std::max(plan.split_tokens, 1024), plan.split_tokens,
+                                                 plan.max_splits > 1);
+        if (c->host && !c->split) return {};
+    }
+    return sp;
+}
+
 }  // namespace
 
 DecodeSchedule decode_schedule(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads, int32_t max_blocks,
                                const int32_t *context_lens_host, int32_t appended, const DecodePlan &plan,
                                hipStream_t stream) {
-    const SmallDecodePlan sp = plan_small(p, stream_cus(p, stream), num_sessions, num_q_heads, max_blocks,
-                                          context_lens_host, appended, plan.recommended());
+    const SmallDecodePlan sp = plan_small_call(p, stream_cus(p, stream), num_sessions, num_q_heads, max_blocks,
+                                               context_lens_host, appended, plan.recommended(), plan);
     if (sp.split_tokens) return DecodeSchedule{sp.split_tokens, context_lens_host != nullptr, false};
     DecodeSchedule sc{plan.split_tokens, false, plan.max_splits > 1};
     if (context_lens_host) {
@@ -1554,8 +1580,8 @@ hipError_t launch_decode(const PoolGeom &p, int layer, int32_t num_sessions, int
     // Small batches.  The room is the query's, so that the same call gives the
     // same result from any workspace of at least that size.
     const int64_t resident = (int64_t)stream_cus(p, stream);
-    const SmallDecodePlan sp = plan_small(p, resident, num_sessions, num_q_heads, max_blocks, context_lens_host,
-                                          a.appended, std::min(workspace_bytes, plan.recommended()));
+    const SmallDecodePlan sp = plan_small_call(p, resident, num_sessions, num_q_heads, max_blocks, context_lens_host,
+                                               a.appended, std::min(workspace_bytes, plan.recommended()), plan);
     if (sp.split_tokens && (sp.single || reinterpret_cast<uintptr_t>(workspace) % 16 == 0)) {
         a.split_tokens = sp.split_tokens;
         a.max_splits = sp.single ? 1 : 0;

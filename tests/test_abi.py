@@ -309,10 +309,10 @@ def test_binding_copy_checks_staging_size(built_lib, binding):
 
 
 # ---- the decode schedule planned on the host (pure host code: no GPU needed)
-def _sched(lib, hkv, hq, lens, maxb, appended=0, host=True):
+def _sched(lib, hkv, hq, lens, maxb, appended=0, host=True, head_dim=128):
     import numpy as np
     h = ctypes.c_void_p()
-    d = _desc(num_layers=1, num_kv_heads=hkv, num_blocks=1 << 20, kv_bytes=1 << 40)
+    d = _desc(num_layers=1, num_kv_heads=hkv, head_dim=head_dim, num_blocks=1 << 20, kv_bytes=1 << 40)
     assert lib.kv_pool_create(ctypes.byref(d), ctypes.byref(h)) == LS_OK
     arr = np.ascontiguousarray(lens, dtype=np.int32)
     t, hp, m = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
@@ -363,6 +363,22 @@ def test_schedule_eight_heads_uses_wide_items(lib):
     lens = np.concatenate([rng.integers(1, 3000, 20), [6000, 6001, 1, 2048]])
     maxb = int(((lens + 1 + 15) // 16).max())
     assert _sched(lib, 8, 16, lens, maxb, appended=1) == (LS_OK, 2048, True, True)
+
+
+@pytest.mark.parametrize("hkv,lens,host,want", [
+    # whole sessions, one per CU, by the persistent kernel: 3 splits each would be 756 workgroups
+    (4, [1100 + s for s in range(63)], True, (2048, True, False)),
+    (8, [360 + 11 * s for s in range(32)], True, (1024, True, False)),
+    # few enough splits, a host plan that merges, or device lengths: splits of 512 in one launch
+    (4, [300 + 25 * s for s in range(16)], True, (512, True, False)),
+    (4, [700 + 55 * s for s in range(35)], True, (512, True, False)),
+    (4, [1100 + s for s in range(63)], False, (512, False, False)),
+    # more than a whole session per CU: split up to two workgroups per CU
+    (8, [446 + 2 * s for s in range(68)], True, (1024, True, False)),
+    (4, [446 + 2 * s for s in range(68)], True, (512, True, False))])
+def test_schedule_of_short_head_dim_64_batches(lib, hkv, lens, host, want):
+    maxb = (max(lens) + 15) // 16
+    assert _sched(lib, hkv, 2 * hkv, lens, maxb, host=host, head_dim=64) == (LS_OK,) + want
 
 
 def test_schedule_rejects_bad_host_lengths(lib):
