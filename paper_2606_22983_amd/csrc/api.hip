@@ -501,6 +501,35 @@ ls_status ls_device_errors(uint32_t *bits) {
     return LS_OK;
 }
 
+// For the tests (not in the header): which schedule a call takes.
+// Tokens per split of the single-launch decode kernel, or 0 for the persistent
+// one; -1 for arguments that a call refuses.
+int32_t ls_internal_small_decode(const ls_kv_pool *pool, int32_t num_sessions, int32_t num_q_heads,
+                                 int32_t max_blocks_per_session, const int32_t *context_lens_host, int32_t appended,
+                                 const void *workspace, size_t workspace_bytes, hipStream_t stream) {
+    int32_t t, h, m;
+    if (ls_decode_schedule(pool, num_sessions, num_q_heads, max_blocks_per_session, context_lens_host, appended,
+                           stream, &t, &h, &m) != LS_OK)
+        return -1;
+    const PoolGeom &p = pool->geom;
+    const DecodePlan plan = plan_decode(p, num_sessions, num_q_heads, max_blocks_per_session);
+    return choose_small(p, stream_cus(p, stream), num_sessions, num_q_heads, max_blocks_per_session, context_lens_host,
+                        appended, workspace, workspace_bytes, plan)
+        .split_tokens;
+}
+
+// Items of a prefill's split plan (0: nothing is split), written to items as
+// PrefillPlanItem; its merged tiles to merged.  -1: more than room.
+int32_t ls_internal_split_prefill(int32_t num_sessions, int32_t num_kv_heads, int32_t group, const int32_t *lens_host,
+                                  int32_t cus, PrefillPlanItem *items, int32_t room, PrefillPlanItem *merged,
+                                  int32_t merged_room, int32_t *num_merged) {
+    int32_t n = 0;
+    return prefill_split_items(num_sessions, num_kv_heads, group, lens_host, cus, items, room, n, merged, merged_room,
+                               *num_merged)
+               ? n
+               : -1;
+}
+
 const char *ls_last_error(void) { return t_last_error; }
 
 const char *ls_version(void) { return "liveserve_kv 0.1.0 (gfx950)"; }

@@ -73,6 +73,24 @@ SmallDecodePlan plan_small(const PoolGeom &p, int64_t cus, int32_t num_sessions,
                            int32_t max_blocks, const int32_t *lens_host, int32_t appended, size_t bytes);
 DecodePlan plan_decode(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads,
                        int32_t max_blocks_per_session);
+// The small batch's plan that a call on a stream of `cus` CUs runs with this
+// workspace, or one without split_tokens: the persistent kernel.
+SmallDecodePlan choose_small(const PoolGeom &p, int64_t cus, int32_t num_sessions, int32_t num_q_heads,
+                             int32_t max_blocks, const int32_t *lens_host, int32_t appended, const void *workspace,
+                             size_t workspace_bytes, const DecodePlan &plan);
+
+// An item of a prefill call that splits keys, where its plan puts it: the
+// slot-th of an XCD's list, over part `chunk` of `chunks` of query tile `tile`
+// of (session, KV head) `pair`; its result goes to `piece` (chunks > 1).
+struct PrefillPlanItem {
+    int32_t xcd, slot, pair, tile, chunk, chunks, piece;
+};
+// For the tests: the items of the split plan of a call, as the kernel reads them,
+// and the tiles its merge adds up (their first piece and chunks).  Counts of 0:
+// nothing is split; false: more items than room.
+bool prefill_split_items(int32_t num_sessions, int32_t num_kv_heads, int32_t group, const int32_t *lens_host,
+                         int64_t cus, PrefillPlanItem *items, int32_t room, int32_t &num_items,
+                         PrefillPlanItem *merged, int32_t merged_room, int32_t &num_merged);
 
 // Most pieces of split query tiles in one prefill call: two waves of one piece per
 // CU.  LS_PREFILL_WORKSPACE_BYTES holds the counters and this many pieces of 256

@@ -1533,11 +1533,21 @@ SmallDecodePlan plan_small_call(const PoolGeom &p, int64_t cus, int32_t num_sess
 
 }  // namespace
 
+SmallDecodePlan choose_small(const PoolGeom &p, int64_t cus, int32_t num_sessions, int32_t num_q_heads,
+                             int32_t max_blocks, const int32_t *lens_host, int32_t appended, const void *workspace,
+                             size_t workspace_bytes, const DecodePlan &plan) {
+    // The room is the query's, so that the same call gives the same result from
+    // any workspace of at least that size.
+    const SmallDecodePlan sp = plan_small_call(p, cus, num_sessions, num_q_heads, max_blocks, lens_host, appended,
+                                               std::min(workspace_bytes, plan.recommended()), plan);
+    return sp.single || reinterpret_cast<uintptr_t>(workspace) % 16 == 0 ? sp : SmallDecodePlan{};
+}
+
 DecodeSchedule decode_schedule(const PoolGeom &p, int32_t num_sessions, int32_t num_q_heads, int32_t max_blocks,
                                const int32_t *context_lens_host, int32_t appended, const DecodePlan &plan,
                                hipStream_t stream) {
-    const SmallDecodePlan sp = plan_small_call(p, stream_cus(p, stream), num_sessions, num_q_heads, max_blocks,
-                                               context_lens_host, appended, plan.recommended(), plan);
+    const SmallDecodePlan sp = choose_small(p, stream_cus(p, stream), num_sessions, num_q_heads, max_blocks,
+                                            context_lens_host, appended, nullptr, plan.recommended(), plan);
     if (sp.split_tokens) return DecodeSchedule{sp.split_tokens, context_lens_host != nullptr, false};
     DecodeSchedule sc{plan.split_tokens, false, plan.max_splits > 1};
     if (context_lens_host) {
@@ -1577,12 +1587,11 @@ hipError_t launch_decode(const PoolGeom &p, int layer, int32_t num_sessions, int
     a.part_acc = reinterpret_cast<float *>(ws + plan.ml_bytes);
     a.num_sessions = num_sessions;
     a.arrived = nullptr;
-    // Small batches.  The room is the query's, so that the same call gives the
-    // same result from any workspace of at least that size.
+    // Small batches.
     const int64_t resident = (int64_t)stream_cus(p, stream);
-    const SmallDecodePlan sp = plan_small_call(p, resident, num_sessions, num_q_heads, max_blocks, context_lens_host,
-                                               a.appended, std::min(workspace_bytes, plan.recommended()), plan);
-    if (sp.split_tokens && (sp.single || reinterpret_cast<uintptr_t>(workspace) % 16 == 0)) {
+    const SmallDecodePlan sp = choose_small(p, resident, num_sessions, num_q_heads, max_blocks, context_lens_host,
+                                            a.appended, workspace, workspace_bytes, plan);
+    if (sp.split_tokens) {
         a.split_tokens = sp.split_tokens;
         a.max_splits = sp.single ? 1 : 0;
         a.arrived = reinterpret_cast<uint64_t *>(ws);

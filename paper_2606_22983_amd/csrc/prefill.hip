@@ -1267,6 +1267,36 @@ bool plan_prefill_split(PrefillPair *pr, int np, int64_t cus, PrefillSplitPlan &
 
 }  // namespace
 
+bool prefill_split_items(int32_t num_sessions, int32_t num_kv_heads, int32_t group, const int32_t *lens_host,
+                         int64_t cus, PrefillPlanItem *items, int32_t room, int32_t &num_items,
+                         PrefillPlanItem *merged, int32_t merged_room, int32_t &num_merged) {
+    num_items = num_merged = 0;
+    PrefillSplitPlan plan;
+    PrefillMergePlan merge;
+    PrefillPair pairs_of[kPlanPairs];
+    int np = 0;
+    int32_t split_tiles = 0;
+    int64_t total = 0;
+    if (!collect_pairs(num_sessions, num_kv_heads, kPreRows / group, lens_host, plan, pairs_of, np) || np == 0) return true;
+    if (!plan_prefill_split(pairs_of, np, cus, plan, merge, split_tiles, total)) return true;
+    if (total > room || split_tiles > merged_room) return false;
+    for (int x = 0; x < kXcds; ++x) {
+        int e = plan.start[x];
+        for (uint32_t slot = 0; slot < plan.total[x]; ++slot) {
+            while (e + 1 < plan.start[x + 1] && plan.before[e + 1] <= slot) ++e;
+            const uint32_t n = (e + 1 < plan.start[x + 1] ? plan.before[e + 1] : plan.total[x]) - plan.before[e];
+            const int32_t t = (int32_t)(n - 1 - (slot - plan.before[e]));
+            items[num_items++] = PrefillPlanItem{x, (int32_t)slot, plan.pair[e], plan.first_tile[e] + t, plan.chunk[e],
+                                                 plan.chunks[e], plan.piece[e] + t * plan.chunks[e] + plan.chunk[e]};
+        }
+    }
+    for (; num_merged < split_tiles; ++num_merged) {
+        const PrefillSplitTile &t = merge.tile[num_merged];
+        merged[num_merged] = PrefillPlanItem{0, num_merged, t.pair, t.tile, 0, t.chunks, t.piece};
+    }
+    return true;
+}
+
 __global__ void clear_counters_kernel(uint32_t *counters) {
     if ((int)threadIdx.x < kPrefillCounters) counters[threadIdx.x] = 0u;
 }

@@ -1,6 +1,7 @@
 """Small decode batches: one workgroup per split, merged by the last of each (session, KV head) to
 finish, without a second launch.  Against the oracle at the edges of blocks, splits and rows, with
 arbitrary workspace contents."""
+import ctypes
 import math
 import os
 import re
@@ -9,6 +10,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2606_22983_amd import workloads as W
 from tests.gpu_util import DevicePool, assert_attn_close, bf16_dev, i32_dev
 from tests.test_gpu_decode import _synthetic
 
@@ -22,11 +24,16 @@ def kv():
     return kv_mod
 
 
-def _small(kv, dp, q, tables, lens, append, host):
-    """The batch runs without the merge kernel, in splits shorter than its longest session."""
-    sc = kv.ls_decode_schedule(dp.pool, q.shape[0], q.shape[1], tables.shape[1],
-                               context_lens_host=lens if host else None, appended=append)
-    return not sc["merge"] and sc["split_tokens"] <= 1024
+def _small(kv, dp, q, tables, lens, append, host, ws=None):
+    """Tokens per split of the single-launch kernel for this call (ws: its workspace), 0: it takes decode_kernel."""
+    n = kv.decode_workspace_bytes(dp.pool, q.shape[0], q.shape[1], tables.shape[1])
+    arr = np.ascontiguousarray(lens, dtype=np.int32)
+    t = kv.raw_library().ls_internal_small_decode(
+        dp.pool.handle, q.shape[0], q.shape[1], tables.shape[1], arr.ctypes.data_as(ctypes.c_void_p) if host else None,
+        int(append), ctypes.c_void_p(0 if ws is None else ws.data_ptr()),
+        ctypes.c_size_t(n if ws is None else ws.numel() * ws.element_size()), None)
+    assert t >= 0
+    return t
 
 
 def _call(kv, dp, q, kn, vn, tables, lens, host, ws, d, lens_host=None):
@@ -55,6 +62,11 @@ def _workspace(kv, dp, q, tables, fill):
     ws = torch.empty((n + 7) // 8, dtype=torch.int64, device="cuda")
     ws.fill_(fill)
     return ws
+
+
+def _unaligned(kv, dp, q, tables):
+    n = kv.decode_workspace_bytes(dp.pool, q.shape[0], q.shape[1], tables.shape[1])
+    return torch.zeros(n // 8 + 2, dtype=torch.int64, device="cuda")[1:]
 
 
 CASES = [
@@ -92,9 +104,11 @@ def test_small_decode_matches_oracle(kv, oracle_lib, hq, hkv, d, lens, append, h
         assert torch.equal(out.view(torch.int16), first.view(torch.int16)), fill
     if append:
         assert np.array_equal(dp.host(), ref_pool)
-    # A workspace that is only 8-byte aligned takes the other schedule.
-    n = kv.decode_workspace_bytes(dp.pool, len(lens), hq, tables.shape[1])
-    other = _call(kv, dp, q, kn, vn, tables, lens, host, torch.zeros(n // 8 + 2, dtype=torch.int64, device="cuda")[1:], d)
+    # A workspace that is only 8-byte aligned takes the other schedule, unless no session is split.
+    other_ws = _unaligned(kv, dp, q, tables)
+    other = _call(kv, dp, q, kn, vn, tables, lens, host, other_ws, d)
+    assert (_small(kv, dp, q, tables, lens, append, host, other_ws) == 0) == (lens.max() + append > _small(
+        kv, dp, q, tables, lens, append, host))
     assert_attn_close(other, ref, "8-byte aligned workspace")
     assert kv.ls_device_errors() == 0
 
@@ -174,3 +188,66 @@ def test_small_decode_errors_and_other_device_lengths(kv, oracle_lib):
     bad[1, 3] = 1 << 29
     _call(kv, dp, q, None, None, bad, lens, False, ws, 128)
     assert kv.ls_device_errors() == kv.LS_DEVERR_BLOCK_ID
+
+
+@pytest.mark.parametrize("kernel", ["small", "persistent"])
+@pytest.mark.parametrize("host", [False, True])
+@pytest.mark.parametrize("hq,hkv,d", [(16, 2, 128), (8, 4, 64)])
+def test_bad_block_ids_and_empty_contexts_in_either_kernel(kv, oracle_lib, hq, hkv, d, host, kernel):
+    """Ids outside the pool, at a split's first block and inside one, and a context without a key, in the
+    single-launch kernel and in decode_kernel: flagged, the block's keys absent, the row zero."""
+    rng = np.random.default_rng(hq + d)
+    lens = np.array([700, 1500, 40, 3000, 1200])
+    pool, tables, q, _, _ = _synthetic(rng, lens, hq, hkv, d, False)
+    dp = DevicePool(kv, pool, d)
+    ws = _workspace(kv, dp, q, tables, -1) if kernel == "small" else _unaligned(kv, dp, q, tables)
+    assert bool(_small(kv, dp, q, tables, lens, False, host, ws)) == (kernel == "small")
+    bad, gone, left = tables.copy(), np.full_like(tables, -1), lens.copy()
+    bad[1, 3], bad[3, 0], bad[3, 100] = 1 << 29, -7, pool.shape[1]
+    for s in range(5):
+        keep = [j for j in range(tables.shape[1]) if not (bad[s, j] != tables[s, j])]
+        gone[s, :len(keep)] = tables[s, keep]
+        left[s] -= 16 * (tables.shape[1] - len(keep))
+    ref = oracle_lib.decode(pool, 16, d, 0, q, gone, left, 1 / math.sqrt(d))
+    kv.ls_device_errors()
+    out = _call(kv, dp, q, None, None, bad, lens, host, ws, d)
+    assert kv.ls_device_errors() == kv.LS_DEVERR_BLOCK_ID
+    assert_attn_close(out, ref, "beside absent blocks")
+    # device lengths with an empty context (host lengths say otherwise, or nothing)
+    dev = lens.copy()
+    dev[2] = 0
+    out = _call(kv, dp, q, None, None, tables, dev, host, ws, d, lens_host=lens)
+    assert kv.ls_device_errors() == kv.LS_DEVERR_LENGTH and bool((out[2] == 0).all())
+    keep = [0, 1, 3, 4]
+    ref = oracle_lib.decode(pool, 16, d, 0, q, tables, lens, 1 / math.sqrt(d))
+    assert_attn_close(out[keep], ref[keep], "beside an empty context")
+
+
+@pytest.mark.parametrize("kernel", ["small", "persistent"])
+def test_scores_at_infinity_and_nan_in_either_kernel(kv, oracle_lib, kernel):
+    """Splits whose scores are all -inf for half of the heads (8 * -3e38 is past the fp32 range) leave the
+    result to the others; a NaN key, or one at +inf, makes its heads NaN and no others."""
+    rng = np.random.default_rng(31)
+    lens, hq, hkv, d = np.array([3000, 600]), 16, 2, 128
+    pool, tables, q, _, _ = _synthetic(rng, lens, hq, hkv, d, False)
+    q[:, :, 0] = 0
+    q[:, ::2, 0] = W.to_bf16(np.float32(8.0))
+    t = np.arange(200, 2000)
+    pool[0, tables[0, t // 16], 0, :, (t % 16) * 8] = W.to_bf16(np.float32(-3e38))
+    dp = DevicePool(kv, pool, d)
+    ws = _workspace(kv, dp, q, tables, -1) if kernel == "small" else _unaligned(kv, dp, q, tables)
+    assert bool(_small(kv, dp, q, tables, lens, False, True, ws)) == (kernel == "small")
+    ref = oracle_lib.decode(pool, 16, d, 0, q, tables, lens, 1 / math.sqrt(d))
+    assert_attn_close(_call(kv, dp, q, None, None, tables, lens, True, ws, d), ref, "scores at -inf")
+    for bits, key in ((0x7FC0, 2900), (0x7F80, 100)):
+        p2 = pool.copy()
+        p2[0, tables[0, key // 16], 0, 1, (key % 16) * 8 + 1] = bits          # dim 1 of KV head 1's key
+        q2 = q.copy()
+        q2[:, :, 1] = W.to_bf16(np.float32(1.0))
+        ref2 = oracle_lib.decode(pool, 16, d, 0, q2, tables, lens, 1 / math.sqrt(d))
+        dp2 = DevicePool(kv, p2, d)
+        out = _call(kv, dp2, q2, None, None, tables, lens, True, ws, d)
+        assert bool(out[0, 8:].isnan().all())
+        assert_attn_close(out[0, :8], ref2[0, :8], "beside a key of %#x" % bits)
+        assert_attn_close(out[1], ref2[1], "another session")
+    assert kv.ls_device_errors() == 0
