@@ -308,6 +308,22 @@ def test_binding_copy_checks_staging_size(built_lib, binding):
         kv.kv_blocks_stash(pool, _i32(3), _bf(3 * pool.block_bytes // 2), max_gbps=-2.0)
 
 
+@pytest.mark.parametrize("missing", ["_raw_stream", "_raw_device"])
+def test_binding_takes_the_public_stream_without_the_private_one(built_lib, binding, monkeypatch, missing):
+    """A torch without the private current-stream entries: the public one's handle is used."""
+    import types
+
+    import torch
+    kv = binding
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x5150))
+    monkeypatch.setattr(kv, "_raw_stream", lambda device: 0x1234 + device)
+    monkeypatch.setattr(kv, "_raw_device", lambda: 1)
+    assert kv._stream(None) == 0x1235
+    monkeypatch.setattr(kv, missing, None)
+    assert kv._stream(None) == 0x5150
+    assert kv._stream(types.SimpleNamespace(cuda_stream=7)) == 7
+
+
 # ---- the decode schedule planned on the host (pure host code: no GPU needed)
 def _sched(lib, hkv, hq, lens, maxb, appended=0, host=True, head_dim=128):
     import numpy as np

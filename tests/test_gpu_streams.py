@@ -32,6 +32,17 @@ def _decode(kv, dp, case, q, tables, lens, stream, ws=None):
     return out, ws
 
 
+def test_the_current_stream_is_torchs(kv, monkeypatch):
+    """Both ways to the current stream's handle, on the default stream and on another."""
+    other = torch.cuda.Stream()
+    for way in ("private", "public"):
+        if way == "public":
+            monkeypatch.setattr(kv, "_raw_stream", None)
+        assert kv._stream(None) == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(other):
+            assert kv._stream(None) == other.cuda_stream == kv._stream(other)
+
+
 @pytest.mark.parametrize("lo,hi", [(0, 24), (40, 256)])
 def test_decode_on_cu_masked_stream_is_bit_identical(kv, lo, hi):
     n_cus = torch.cuda.get_device_properties(0).multi_processor_count
