@@ -1323,9 +1323,19 @@ hipError_t launch_prefill(const PoolGeom &p, int layer, int32_t num_sessions, in
     a.max_blocks = max_blocks;
     a.scale_log2 = scale * kLog2eP;
     a.err = err;
-    // Half a tile of padding per turn, on average: from an eighth of the rows on,
-    // waves without rows or keys skip their work.
-    const bool skip = 4LL * num_sessions * (kPreRows / a.group) >= total_tokens;
+    // Waves skip what none of their rows sees where that shortens the longest
+    // tiles: the longest turn fits half a query tile, so that no SIMD runs two
+    // waves with rows (2 turns of 18-24 tokens over 3854-6172, 4 heads per KV
+    // head: 119.4 -> 85.7 us; 18 batches, 1.04 to 1.59 times as fast); or padding
+    // is an eighth of the rows (half a tile per turn, on average) and turns are
+    // long beside their contexts, so that the causal limits of a tile's waves
+    // differ (8 first turns of 50-700 tokens: 22.3 -> 20.7 us; 11 batches, 1.00 to
+    // 1.04).  Elsewhere full tiles take as long and pay for the second loop
+    // bound: of 15 batches with that padding 8 were 1 to 3% slower (1 turn of 36
+    // tokens over 20,000, 8 heads per KV head: 409.4 -> 421.3), 5 1 to 3% faster.
+    const int64_t rows_longest = (int64_t)max_new_len * a.group;
+    const bool skip = rows_longest <= kPreRows / 2 || (4LL * num_sessions * (kPreRows / a.group) >= total_tokens &&
+                                                       (int64_t)max_blocks * kBlock <= 8LL * max_new_len);
     a.resident = 0;
     a.queue = nullptr;
     a.part_ml = nullptr;
