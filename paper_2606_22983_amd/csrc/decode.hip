@@ -1165,10 +1165,13 @@ SmallDecodePlan plan_small(const PoolGeom &p, int64_t cus, int32_t num_sessions,
     const int64_t hkv = p.num_kv_heads;
     if (p.head_dim != 128) cus = p.num_cus > 0 ? p.num_cus : 256;
     if (num_sessions > kMaxBatch) return none;
-    int64_t longest = (int64_t)max_blocks * kBlock;
+    int64_t longest = (int64_t)max_blocks * kBlock, total = 0;
     if (lens_host) {
         longest = 1;
-        for (int32_t s = 0; s < num_sessions; ++s) longest = std::max(longest, (int64_t)lens_host[s] + appended);
+        for (int32_t s = 0; s < num_sessions; ++s) {
+            longest = std::max(longest, (int64_t)lens_host[s] + appended);
+            total += (int64_t)lens_host[s] + appended;
+        }
     }
     const int G = num_q_heads / p.num_kv_heads;
     auto pad = [](size_t b) { return (b + 255) & ~(size_t)255; };
@@ -1180,10 +1183,26 @@ SmallDecodePlan plan_small(const PoolGeom &p, int64_t cus, int32_t num_sessions,
         if (T < kMaxSplitTokens && (int64_t)T * T < 8 * longest) continue;
         SmallDecodePlan plan;
         if (T >= longest) {
-            // No session is split: no partials and no counts, whatever the batch
-            // (but the host plan's prefetch wins on many 1024-token items at
-            // D = 64: 500 sessions of 300-1000 keys at 2 heads, 37.5 against 38.1 us).
-            if (!wide && T == kMaxSplitTokens && lens_host && num_sessions * hkv > 2 * cus) return none;
+            // No session is split: no partials and no counts, whatever the batch.
+            // But with more than one workgroup per CU the host's plan for the
+            // persistent kernel pairs long sessions with short ones, which wins
+            // where the mean length is well below the longest.
+            // D = 64, splits of 1024: below 3/4 of the longest with up to two per
+            // CU (308 sessions of up to 835 keys at 1 head, mean 0.65: 11.5 us,
+            // 15.6 here; of 7 such batches 5 were 4-26% slower here, one 7%
+            // faster; of 10 more even ones 8 up to 8% faster, two up to 5%
+            // slower), and any batch beyond two, as before this kernel (47
+            // batches: up to four per CU 20% slower to 4% faster here, beyond
+            // four 0-13% faster, which is left).
+            // D = 128, splits from 512 on, one or two query heads per KV head:
+            // below 3/5 of the longest (8 of 9 batches 1-9% slower here, one 1%
+            // faster; with more query heads nine are 4-26% faster here).
+            if (lens_host && num_sessions * hkv > cus) {
+                const int64_t even = longest * num_sessions;
+                if (wide ? T > 256 && G <= 2 && 5 * total < 3 * even
+                         : T == kMaxSplitTokens && (num_sessions * hkv > 2 * cus || 4 * total < 3 * even))
+                    return none;
+            }
             plan.split_tokens = T;
             plan.rows = num_sessions;
             plan.single = true;

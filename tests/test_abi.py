@@ -397,6 +397,28 @@ def test_schedule_of_short_head_dim_64_batches(lib, hkv, lens, host, want):
     assert _sched(lib, hkv, 2 * hkv, lens, maxb, host=host, head_dim=64) == (LS_OK,) + want
 
 
+@pytest.mark.parametrize("hq,hkv,d,lens,want", [
+    # uneven whole sessions, more than one per CU: decode_kernel by the host's plan
+    (1, 1, 64, [235 + 2 * s for s in range(300)], 0), (2, 2, 128, [50 + 4 * s for s in range(160)], 0),
+    (4, 2, 128, [60 + 2 * s for s in range(200)], 0),
+    # even ones, at most one per CU, more query heads per KV head, splits of 256, or device lengths: one launch
+    (1, 1, 64, [750 + s % 90 for s in range(300)], 1024), (1, 1, 64, [235 + 2 * s for s in range(256)], 1024),
+    (2, 2, 128, [500 + s for s in range(160)], 768), (2, 2, 128, [100 + 5 * s for s in range(128)], 768),
+    (8, 2, 128, [50 + 4 * s for s in range(160)], 768), (2, 2, 128, [10 + s for s in range(200)], 256)])
+def test_schedule_of_uneven_whole_sessions(lib, hq, hkv, d, lens, want):
+    import numpy as np
+    h = ctypes.c_void_p()
+    desc = _desc(num_layers=1, num_kv_heads=hkv, head_dim=d, num_blocks=1 << 20, kv_bytes=1 << 40)
+    assert lib.kv_pool_create(ctypes.byref(desc), ctypes.byref(h)) == LS_OK
+    arr = np.ascontiguousarray(lens, dtype=np.int32)
+    for host in (True, False):
+        got = lib.ls_internal_small_decode(h, len(lens), hq, (max(lens) + 15) // 16,
+                                           arr.ctypes.data_as(ctypes.c_void_p) if host else None, 0, None,
+                                           ctypes.c_size_t(1 << 40), None)
+        assert (got == want) if host else got > 0
+    lib.kv_pool_destroy(h)
+
+
 def test_schedule_rejects_bad_host_lengths(lib):
     assert _sched(lib, 2, 16, [5, 0, 7], 10)[0] == LS_EINVAL          # an empty context
     assert _sched(lib, 2, 16, [5, 0, 7], 10, appended=1)[0] == LS_OK
