@@ -1146,12 +1146,18 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(DecodeArgs
 // (session, KV head) has one workgroup, and any number of them is taken (200
 // sessions of 50-300 keys at 4 heads 37.6 -> 25.3 us, 64 of 300-900 with device
 // lengths 30.2 -> 20.8).
-// At D = 128 the CUs are the stream's.  On a stream of 24 of the 256 CUs, with
-// splits chosen for 256 against the persistent kernel: one session of 16,000
-// keys 52.1 and 37.4 us, 8 of up to 16k 144 and 122, 16 of 300-2500 75.7 and
-// 52.6.  At D = 64 they are the device's: two workgroups of 89 registers fit a
-// CU and the third waits for a place, and still, with device lengths, this
-// kernel is the faster at any number of them (48 sessions of 100-3000 keys, 652
+// With host lengths at D = 128 the CUs are the stream's.  On a stream of 24 of
+// the 256 CUs, with splits chosen for 256 against the persistent kernel: one
+// session of 16,000 keys 52.1 and 37.4 us, 8 of up to 16k 144 and 122, 16 of
+// 300-2500 75.7 and 52.6.  With device lengths they are the device's, so that a
+// result does not depend on the stream's mask.  That costs the batches with the
+// most workgroups on the smallest masks (24 CUs: 16 of 300-2500 at 4 heads 72.6
+// -> 90.9 us against the persistent kernel, one of 16,000 50.1 -> 54.0) and
+// suits the others (24 CUs: 8 of 300-2500 at 2 heads 23.3 -> 19.7, 64 of 50-250
+// 68.4 -> 28.0; of 12 batches on 128 CUs 11 are 1.03 to 1.9 times as fast).
+// At D = 64 they are the device's too: two workgroups of 89 registers fit a CU
+// and the third waits for a place, and still, with device lengths, this kernel
+// is the faster at any number of them (48 sessions of 100-3000 keys, 652
 // workgroups: 24.6 -> 19.9 us on 256 CUs, 33.1 -> 26.3 on 128, 145 -> 108 on 24).
 struct SmallSize {
     int tokens, per_cu;
@@ -1163,7 +1169,7 @@ SmallDecodePlan plan_small(const PoolGeom &p, int64_t cus, int32_t num_sessions,
                            int32_t max_blocks, const int32_t *lens_host, int32_t appended, size_t bytes) {
     const SmallDecodePlan none;
     const int64_t hkv = p.num_kv_heads;
-    if (p.head_dim != 128) cus = p.num_cus > 0 ? p.num_cus : 256;
+    if (p.head_dim != 128 || !lens_host) cus = p.num_cus > 0 ? p.num_cus : 256;
     if (num_sessions > kMaxBatch) return none;
     int64_t longest = (int64_t)max_blocks * kBlock, total = 0;
     if (lens_host) {

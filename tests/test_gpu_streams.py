@@ -73,8 +73,9 @@ def test_decode_on_cu_masked_stream_is_bit_identical(kv, lo, hi):
     (32, 4, 128, [9000]), (16, 2, 128, [300, 2500, 1, 1200, 900, 2000]), (32, 4, 128, [700] * 6), (16, 4, 64, [100, 3000, 513]),
     (8, 8, 64, [500, 40, 512])])
 def test_small_decode_on_cu_masked_streams(kv, oracle_lib, hq, hkv, d, lens, host):
-    """Small batches on streams of 8, 24 and 128 CUs in turn, one workspace: the split size, and the
-    kernel, follow the stream's CUs at D = 128, and the results are the oracle's on each."""
+    """Small batches on streams of 8, 24 and 128 CUs in turn, one workspace: with host lengths the split
+    size, and the kernel, follow the stream's CUs at D = 128; with device lengths the bits are those of
+    the whole device.  The results are the oracle's on each."""
     rng = np.random.default_rng(len(lens) + d)
     lens = np.array(lens)
     pool, tables, q, _, _ = _synthetic(rng, lens, hq, hkv, d, False)
@@ -83,6 +84,9 @@ def test_small_decode_on_cu_masked_streams(kv, oracle_lib, hq, hkv, d, lens, hos
     ws = torch.full((kv.decode_workspace_bytes(dp.pool, len(lens), hq, tables.shape[1]),), 0x5A, dtype=torch.uint8,
                     device="cuda")
     qd, td, ld = bf16_dev(q), i32_dev(tables), i32_dev(lens)
+    full = torch.empty_like(qd)
+    kv.paged_attn_decode(dp.pool, 0, qd, td, ld, 1 / math.sqrt(d), full, ws, context_lens_host=lens if host else None)
+    assert_attn_close(full, ref, "small decode")
     merges = []
     for hi in (8, 24, 128, 8):
         made = cu_masked_stream(0, hi)
@@ -96,6 +100,8 @@ def test_small_decode_on_cu_masked_streams(kv, oracle_lib, hq, hkv, d, lens, hos
                                  context_lens_host=lens if host else None)
             stream.synchronize()
             assert_attn_close(out, ref, "small decode on %d CUs" % hi)
+            if not host:
+                assert torch.equal(out.view(torch.int16), full.view(torch.int16)), hi
             merges.append(kv.ls_decode_schedule(dp.pool, len(lens), hq, tables.shape[1], lens if host else None,
                                                 stream=stream)["merge"])
         finally:
@@ -103,9 +109,11 @@ def test_small_decode_on_cu_masked_streams(kv, oracle_lib, hq, hkv, d, lens, hos
             destroy_stream(handle)
     assert kv.ls_device_errors() == 0
     # 9 to 18 splits of 9000 keys at 4 heads are few on 128 CUs, and too many on 8
-    if len(lens) == 1:
-        assert not kv.ls_decode_schedule(dp.pool, 1, hq, tables.shape[1], lens if host else None)["merge"]
+    if len(lens) == 1 and host:
+        assert not kv.ls_decode_schedule(dp.pool, 1, hq, tables.shape[1], lens)["merge"]
         assert merges[0] and merges[3] and not merges[2]
+    if not host:
+        assert not any(merges)
 
 
 def test_split_prefill_on_cu_masked_stream(kv, oracle_lib):
