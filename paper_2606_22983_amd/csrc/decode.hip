@@ -1138,14 +1138,19 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(DecodeArgs
 // not taken: there the partials a split's last workgroup reads back (4096 L / T
 // bytes at D = 128) outweigh its own keys (512 T).  Of the others, in this
 // order: 256 or 512 tokens at one workgroup per CU, 256 at two (106 registers
-// allow it), longer ones; at D = 64, 512 at three.  Measured against the
-// two-launch schedules on 35 shapes: one session of 1789 keys 13.9 -> 7.4 us,
-// 16 of 300-4000 (device lengths) 19.3 -> 15.4, 32 of 1000-6000 at 2 heads
-// 30.7 -> 24.2, none slower.  Past one wave the persistent kernel's prefetch
-// across items wins, unless no session is longer than a split: then each
-// (session, KV head) has one workgroup, and any number of them is taken (200
-// sessions of 50-300 keys at 4 heads 37.6 -> 25.3 us, 64 of 300-900 with device
-// lengths 30.2 -> 20.8).
+// allow it), longer ones; at D = 64, 512 at three.  Past one wave the
+// persistent kernel's prefetch across items wins, unless no session is longer
+// than a split: then each (session, KV head) has one workgroup, and any number
+// of them is taken, but for uneven batches (below).
+// Measured against the persistent kernel and its merge launch on 508 random
+// batches that this rule takes (1 to 700 sessions of up to 20,000 keys, either
+// kind of lengths and head_dim): 1.43 times as fast in the geometric mean, up
+// to 2.2; four are more than 2% slower (2.2-4.4%: 22 sessions of 736-783 keys at
+// 8 heads, device lengths, 21.6 -> 22.6 us).  One session of 1789 keys 13.9 ->
+// 7.4 us, 16 of 300-4000 (device lengths) 19.3 -> 15.4, 200 of 50-300 at 4 heads
+// 37.6 -> 25.3.  The least gain is at the rule's edges: of 183 batches of
+// 60-2200 (session, KV head)s and sessions of 257 to 1023 keys, nine are more
+// than 2% slower (160 sessions of 264-952 keys at 2 heads 19.8 -> 22.4 us).
 // With host lengths at D = 128 the CUs are the stream's.  On a stream of 24 of
 // the 256 CUs, with splits chosen for 256 against the persistent kernel: one
 // session of 16,000 keys 52.1 and 37.4 us, 8 of up to 16k 144 and 122, 16 of
@@ -1214,8 +1219,12 @@ SmallDecodePlan plan_small(const PoolGeom &p, int64_t cus, int32_t num_sessions,
             plan.single = true;
             return plan;
         }
-        // A table far wider than the contexts leaves few, long splits: 8
-        // sessions of 500-2500 keys in 16k-token tables took 17.4 us against 16.2.
+        // A table far wider than the contexts leaves few, long splits (8
+        // sessions of 500-2500 keys in tables of 16k at 4 heads: 14.8 us, 14.4
+        // without), so device lengths keep the persistent kernel here.  Of 17
+        // batches that this leaves out 5 are 0-3% faster for it and 12 slower,
+        // those with the fewest splits most (4 sessions of 1000-40,000 keys in
+        // tables of 64k at 2 heads, D = 64: 21.7 us, 15.1 without).
         if (!lens_host && T == kMaxSplitTokens) continue;
         int64_t rows = 0;                          // of the grid
         double resident;                           // workgroups with keys, expected

@@ -1033,14 +1033,17 @@ int32_t key_parts(int32_t tiles, int32_t target) { return (tiles + target - 1) /
 // a workgroup's serial pass over its keys decides the call's duration: 40 items
 // (one turn of 301 tokens at 32/4 heads) kept 40 of 256 CUs busy for 198 us.
 // Such items are split into parts of their keys, as many as fill the CUs: that
-// call went from 200 to 61 us, and four turns (268 items of 165-268 key tiles,
-// a second wave of 12) from 505 to 455 us.
-// Estimates, in key tiles of one workgroup (about 1.1 us each at D = 128): an
-// unsplit call lasts as long as its total over the CUs, and at least as w + 1
-// items of the length of the (w C + 1)-th longest, which some CU must run; a
-// split one lasts its whole waves plus m waves of parts and the merge.  The
-// least estimate wins, and must win by kSplitGain.  Batches of many waves stay
-// whole (their last wave is a small share and the queue evens it out).
+// call went from 200 to 59 us, and four turns (268 items of 165-268 key tiles,
+// a second wave of 12) from 512 to 443 us.  37 random calls that are split (1 to
+// 40 turns): 1.05 to 14 times as fast.
+// Estimates, in key tiles of one workgroup: an unsplit call lasts as long as its
+// total over the CUs, and at least as w + 1 items of the length of the
+// (w C + 1)-th longest, which some CU must run; a split one lasts its whole
+// waves plus m waves of parts and the merge.  The least estimate wins, and must
+// win by kSplitGain.  Batches of many waves stay whole (their last wave is a
+// small share and the queue evens it out).  A key tile takes 1.6-1.75 us at
+// D = 128, so the costs below, which were chosen by trial, stand for 5 us per
+// item (one turn shows 8) and 10 for the merge (its launch takes 7).
 constexpr int kMinPartTiles = 16;      // key tiles per part: below, an item's start and the merge cost what a part saves
 constexpr int kMaxParts = 32;
 constexpr int kSplitMaxWaves = 6;      // whole waves from which nothing is split
